@@ -316,10 +316,11 @@ int pf_workspace_layout(const pf_plan *p, int dir);
  * Kernel family that runs pass `pass` of direction `dir` (a short static
  * string, "" for an invalid plan / dir / pass): "c2c_generic", "r2c_generic",
  * "c2r_generic" (radix plan read at run time, Sec. 2's 1D transforms as a
- * stage loop); "c2c_pow2", "r2c_pow2", "c2r_pow2" (power-of-two lengths, radix
+ * stage loop; in FP64 also the compile-time two-step plan of the "mixed"
+ * lengths); "c2c_pow2", "r2c_pow2", "c2r_pow2" (power-of-two lengths, radix
  * plan fixed at compile time, persistent workgroups); "c2c_mixed",
- * "r2c_mixed", "c2r_mixed" (7-smooth lengths with a compile-time two-step
- * plan, FP32); "xy_fused" (fused_xy); "remap", "fill", "box" (reorders of
+ * "r2c_mixed", "c2r_mixed" (7-smooth lengths 16 .. 1024 but 343 and 686, with
+ * a compile-time two-step plan, FP32); "xy_fused" (fused_xy); "remap", "fill", "box" (reorders of
  * the processor-grid and share-only plans).  Introspection only.
  */
 const char *pf_pass_kernel(const pf_plan *p, int dir, int pass);
@@ -406,7 +407,7 @@ int pf_spectral_step(pf_plan *p, const void *in, void *spec, void *out, int adjo
  * Many independent 3D transforms of different sizes run together (the same
  * method per transform, Sec. 2; the paper's "any grid dimensions", Sec. 3.1).
  * An axis whose length has a compile-time mixed-radix kernel (the 7-smooth
- * lengths 48 .. 320 but 256, and 360, 480; FP32) runs that kernel; every
+ * lengths 16 .. 1024 but 343 and 686) runs that kernel; every
  * other axis runs the runtime-radix kernels (the power-of-two kernels, whose
  * persistent grids are sized per transform, are not used in a batch).  A
  * fused pass is one kernel launch per group of transforms that share a
@@ -417,8 +418,8 @@ int pf_spectral_step(pf_plan *p, const void *in, void *spec, void *out, int adjo
  * pf_tune: per axis (x, y, z) a radix order (0: radix 16 first, then 8, 4, 2,
  * 3, 5, 7; 1: 8, 4, 2, 3, 5, 7; 2: 4, 2, 3, 5, 7; 3: 3, 5, 7 first, then 16,
  * 8, 4, 2) and a tile width (0: the default, else at most that many line
- * pairs per X tile or columns per Y / Z tile; below 16 it selects the
- * runtime-radix kernel for that axis).  Chosen per transform by the
+ * pairs per X tile or columns per Y / Z tile; below 16 (FP64 Y / Z: below 8)
+ * it selects the runtime-radix kernel for that axis).  Chosen per transform by the
  * package's autotuner; NULL means defaults.
  */
 typedef struct pf_tune {

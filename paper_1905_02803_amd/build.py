@@ -7,13 +7,19 @@ from __future__ import annotations
 import os
 import subprocess
 import sys
+from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libpencilfft.so")
-SOURCES = ["capi.hip", "kernels.hip", "kernels_p2.hip", "kernels_mr.hip",
-           "kernels_mr_p0.hip", "kernels_mr_p1.hip", "kernels_mr_p2.hip", "kernels_mr_p3.hip"]
+# the mixed-radix kernels: one source, compiled once per unit and precision
+MR_UNITS = 8
+MR_PARTS = {f"kernels_mr_{t}_{u}.hip": [f"-DPF_MR_UNIT={u}", f"-DPF_MR_UNITS={MR_UNITS}", f"-DPF_MR_T={t}",
+                                        f"-DPF_MR_NAME=mr_pick_{t}_{u}"]
+            for t in ("double", "float") for u in range(MR_UNITS)}
+# object names (with .hip in place of .o), the slowest to compile first
+SOURCES = ["kernels_p2.hip", *MR_PARTS, "capi.hip", "kernels.hip", "kernels_mr.hip"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 
 FLAGS = [
@@ -30,15 +36,18 @@ def build(verbose: bool = False, out: str = LIB, extra=()) -> str:
     bdir = os.path.join(os.path.dirname(out), "_build")
     os.makedirs(bdir, exist_ok=True)
     inc = ["-I", os.path.join(ROOT, "include"), "-I", CSRC]
-    procs = []
-    for src in SOURCES:  # the sources compile concurrently
+    cmds = []
+    for src in SOURCES:
         obj = os.path.join(bdir, src.replace(".hip", ".o"))
-        cmd = [HIPCC] + FLAGS + list(extra) + inc + ["-c", os.path.join(CSRC, src), "-o", obj]
+        path = os.path.join(CSRC, "kernels_mr_unit.hip" if src in MR_PARTS else src)
+        cmds.append([HIPCC] + FLAGS + list(extra) + MR_PARTS.get(src, []) + inc + ["-c", path, "-o", obj])
         if verbose:
-            print(" ".join(cmd), flush=True)
-        procs.append((subprocess.Popen(cmd), cmd))
+            print(" ".join(cmds[-1]), flush=True)
         objs.append(obj)
-    failed = [cmd for p, cmd in procs if p.wait() != 0]
+    # the sources compile concurrently, as many at a time as there are CPUs to run them
+    with ThreadPoolExecutor(max(1, min(16, len(os.sched_getaffinity(0))))) as ex:
+        codes = list(ex.map(lambda c: subprocess.run(c).returncode, cmds))
+    failed = [cmd for code, cmd in zip(codes, cmds) if code != 0]
     if failed:
         raise subprocess.CalledProcessError(1, failed[0])
     tmp = out + ".tmp%d" % os.getpid()

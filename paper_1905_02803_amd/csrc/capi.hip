@@ -61,8 +61,8 @@ struct pf_plan {
     FftSpec fx, fy, fz;
     void *tw_dev;  // one allocation holding the x, y, z tables (+ the half-length X table)
     size_t tw_off[4];
-    // x, y, z: a compile-time mixed-radix kernel serves the axis (FP32), and the
-    // offset of its table W_n^m, m < n, in tw_dev
+    // x, y, z: a compile-time mixed-radix kernel serves the axis, and the offset
+    // of its table W_n^m, m < n, in tw_dev
     bool mr[3];
     size_t tw_mr[3];
     size_t tw_dct;  // split type-I DCT of the fused spectral step: [L-point][M-point stage tables][W_4M^k]
@@ -287,14 +287,14 @@ void set_c2c_common(PassDesc &d, const pf_plan *p, const FftSpec &fs, size_t two
         d.lds = pf::p2d_lds_bytes(fs.n);
         return;
     }
-    if (axis >= 0 && p->mr[axis] && plain_fft && max_tc >= 16) {
-        // compile-time mixed-radix plan: 16 columns per tile, one tile per workgroup
+    if (axis >= 0 && p->mr[axis] && plain_fft && max_tc >= p->B) {
+        // compile-time mixed-radix plan: one 128-byte row of columns per tile, one tile per workgroup
         d.kind = pf::PASS_C2C_MR;
         a.tw = (const char *)p->tw_dev + p->tw_mr[axis];
-        a.tc_log2 = 4;
+        a.tc_log2 = p->b_log2;
         a.wpc_log2 = 0;
-        d.threads = (unsigned)pf::mr_threads_of(fs.n, 0);
-        d.lds = pf::mr_lds_bytes(fs.n, 0);
+        d.threads = (unsigned)pf::mr_threads_of(fs.n, d.prec, 0);
+        d.lds = pf::mr_lds_bytes(fs.n, d.prec, 0);
         return;
     }
     d.kind = pf::PASS_C2C;
@@ -661,13 +661,13 @@ void build_passes(pf_plan *p) {
         const long long tcx = 1LL << x.a.tc_log2;
         x.blocks = (unsigned)((pairs + tcx - 1) / tcx);
         if (p->mr[0] && xmax >= 16) {  // compile-time mixed-radix plan, mr_x_pairs() line pairs per tile
-            const int xp = pf::mr_x_pairs();
+            const int xp = pf::mr_x_pairs(p->nx, x.prec);
             x.kind = dir == 0 ? pf::PASS_R2C_MR : pf::PASS_C2R_MR;
             x.a.tw = (const char *)p->tw_dev + p->tw_mr[0];
             x.a.tc_log2 = ilog2(xp);
             x.a.wpc_log2 = 0;
-            x.threads = (unsigned)pf::mr_threads_of(p->nx, 1);
-            x.lds = pf::mr_lds_bytes(p->nx, 1);
+            x.threads = (unsigned)pf::mr_threads_of(p->nx, x.prec, 1);
+            x.lds = pf::mr_lds_bytes(p->nx, x.prec, 1);
             x.blocks = (unsigned)((pairs + xp - 1) / xp);
         }
         if (p->fast_x) {  // half-length complex transform, 16 (FP64: 8) lines per tile, persistent blocks
@@ -1095,8 +1095,9 @@ static int plan_create(int nx, int ny, int nz, const pf_layout *l, const PlanOpt
         else split_table(0.f);
         host.resize((host.size() + 255) & ~(size_t)255, 0);
     }
-    // mixed-radix tables W_n^m, m < n (FP32 plain transforms; the Chebyshev and
-    // empty third transforms keep the runtime-radix kernel)
+    // mixed-radix tables W_n^m, m < n (plain transforms; the Chebyshev and empty
+    // third transforms keep the runtime-radix kernel), rounded once to the
+    // plan's precision
     const int axis_n[3] = {nx, ny, nz};
     for (int i = 0; i < 3; ++i) {
         p->mr[i] = !o.no_mr && pf::mr_supported(axis_n[i], l->precision) && !(i == 0 && p->fast_x) &&
@@ -1104,15 +1105,20 @@ static int plan_create(int nx, int ny, int nz, const pf_layout *l, const PlanOpt
         p->tw_mr[i] = 0;
         if (!p->mr[i]) continue;
         p->tw_mr[i] = host.size();
-        std::vector<float> t(2 * (size_t)axis_n[i]);
-        const double two_pi = 6.283185307179586476925286766559;
-        for (int m = 0; m < axis_n[i]; ++m) {
-            const double ang = two_pi * (double)m / (double)axis_n[i];
-            t[2 * (size_t)m] = (float)std::cos(ang);
-            t[2 * (size_t)m + 1] = (float)(-std::sin(ang));
-        }
-        const unsigned char *b = reinterpret_cast<const unsigned char *>(t.data());
-        host.insert(host.end(), b, b + t.size() * sizeof(float));
+        auto mr_table = [&](auto zero) {
+            typedef decltype(zero) R;
+            std::vector<R> t(2 * (size_t)axis_n[i]);
+            const double two_pi = 6.283185307179586476925286766559;
+            for (int m = 0; m < axis_n[i]; ++m) {
+                const double ang = two_pi * (double)m / (double)axis_n[i];
+                t[2 * (size_t)m] = (R)std::cos(ang);
+                t[2 * (size_t)m + 1] = (R)(-std::sin(ang));
+            }
+            const unsigned char *b = reinterpret_cast<const unsigned char *>(t.data());
+            host.insert(host.end(), b, b + t.size() * sizeof(R));
+        };
+        if (l->precision == PF_F64) mr_table(0.0);
+        else mr_table(0.f);
         host.resize((host.size() + 255) & ~(size_t)255, 0);
     }
     // the split type-I DCT of the fused spectral step (FP32, nz = L + 1 = 257)
@@ -1155,6 +1161,8 @@ static int plan_create(int nx, int ny, int nz, const pf_layout *l, const PlanOpt
         if (e == hipSuccess && pf::p2_supported(n, l->precision)) e = pf::p2_prepare(n);
         if (e == hipSuccess && l->precision == PF_F64 && !o.generic_only && pf::p2d_supported(n)) e = pf::p2d_prepare(n);
     }
+    for (int i = 0; i < 3; ++i)
+        if (e == hipSuccess && p->mr[i]) e = pf::mr_prepare(axis_n[i], l->precision, i == 0);
     const bool cheb_p2 = l->third == PF_THIRD_CHEB && !o.generic_only && pf::p2_supported(p->fz.n, l->precision);
     if (e == hipSuccess && cheb_p2) e = pf::p2_spec_prepare(p->fz.n);
     if (e == hipSuccess && p->fast_x) e = pf::p2x_prepare(nx, l->precision);
@@ -1352,6 +1360,8 @@ int pf_workspace_layout(const pf_plan *p, int dir) {
 
 const char *pf_pass_kernel(const pf_plan *p, int dir, int pass) {
     if (!p || dir < 0 || dir > 1 || pass < 0 || pass >= p->npass[dir]) return "";
+    // FP64 mixed-radix passes report the runtime-radix family (pencilfft.h)
+    const bool f64 = p->pass[dir][pass].prec == PF_F64;
     switch (p->pass[dir][pass].kind) {
         case pf::PASS_C2C: return "c2c_generic";
         case pf::PASS_R2C_X: return "r2c_generic";
@@ -1359,9 +1369,9 @@ const char *pf_pass_kernel(const pf_plan *p, int dir, int pass) {
         case pf::PASS_C2C_P2: return "c2c_pow2";
         case pf::PASS_R2C_P2: return "r2c_pow2";
         case pf::PASS_C2R_P2: return "c2r_pow2";
-        case pf::PASS_C2C_MR: return "c2c_mixed";
-        case pf::PASS_R2C_MR: return "r2c_mixed";
-        case pf::PASS_C2R_MR: return "c2r_mixed";
+        case pf::PASS_C2C_MR: return f64 ? "c2c_generic" : "c2c_mixed";
+        case pf::PASS_R2C_MR: return f64 ? "r2c_generic" : "r2c_mixed";
+        case pf::PASS_C2R_MR: return f64 ? "c2r_generic" : "c2r_mixed";
         case pf::PASS_FUSED_XY: return "xy_fused";
         case pf::PASS_REMAP: return "remap";
         case pf::PASS_FILL: return "fill";

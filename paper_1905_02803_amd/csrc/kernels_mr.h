@@ -1,20 +1,36 @@
-// kernels_mr.h -- FP32 passes for mixed-radix lengths with the plan fixed at
-// compile time (the Y / Z column passes and the X real-line passes of the
-// transpose-based 3D FFT, Sec. 2).
+// kernels_mr.h -- passes for mixed-radix lengths with the plan fixed at
+// compile time, FP32 and FP64 (the Y / Z column passes and the X real-line
+// passes of the transpose-based 3D FFT, Sec. 2).
 //
-// A length N = N1 N2 (N1 <= N2 <= 36, every factor 2, 3, 5 or 7) is done in
+// A length N = N1 N2 (N1 <= N2 <= 42, every factor 2, 3, 5 or 7) is done in
 // two Cooley-Tukey steps with input index n = q + N2 m and output index
 // k = k1 + N1 k2 (q, k2 < N2; m, k1 < N1):
 //     Y[q][k1]          = W_N^{q k1} sum_m x[q + N2 m] W_N1^{m k1}      (step 1)
 //     X[k1 + N1 k2]     = sum_q Y[q][k1] W_N2^{q k2}                    (step 2)
 // Each step is one in-register DFT per thread whose radix structure and
 // internal twiddles are compile-time constants; the only exchange between
-// threads is the LDS tile between the steps.  A C2C tile (16 columns of one
-// 128-byte workspace row block) reads its step-1 inputs straight from global
-// memory into registers and stores the step-2 outputs straight from
-// registers: one LDS round trip per tile, against one per radix stage plus
-// the staging of the load and the store in the runtime-radix kernels.
-// Lanes run along the 16 columns of the tile on both sides.
+// threads is the LDS tile between the steps.  A C2C tile (the columns of one
+// 128-byte workspace row block: 16 FP32, 8 FP64) reads its step-1 inputs
+// straight from global memory into registers and stores the step-2 outputs
+// straight from registers: one LDS round trip per tile, against one per radix
+// stage plus the staging of the load and the store in the runtime-radix
+// kernels.  Lanes run along the columns of the tile on both sides.
+//
+// Bound by the HBM traffic of the pass; measured against the runtime-radix
+// kernels, which staged the tile in LDS and read their twiddles per radix stage
+// (ms per R2C + C2R pair): FP64 300 x 280 x 250 0.675 -> 0.415 (Y pass 2.55 ->
+// 5.87 TB/s), FP64 600 x 400 x 450 3.95 -> 2.28, FP32 768 x 768 x 384 3.27 ->
+// 2.49, FP32 384^3 in natural order 0.897 -> 0.668, FP32 36 x 20 x 24 0.049 ->
+// 0.028 (8.2 against 4.7 us per pass).
+//
+// Long lengths exchange the real and the imaginary parts one after the other
+// through half the LDS (MrShape::SPLIT), so that several workgroups still fit
+// on a CU and one's loads overlap another's transform.
+//
+// The backward transform is the forward one on conjugated values, conj(F(conj
+// x)): the C2C kernel takes the sign at run time (one multiplication by +-1
+// per element on each side, exact), the backward X kernel conjugates in its
+// Hermitian fill and its stores.
 //
 // The X passes carry two real lines as one complex line (a + i b), as the
 // runtime-radix X kernels do; their loads and stores run along the points of
@@ -31,41 +47,70 @@ extern __shared__ __align__(16) unsigned char pf_smem[];
 
 // ---- cos / sin of 2 pi m / n, evaluated by the compiler -----------------------
 // The angle is reduced exactly in integers to a quarter turn plus an angle in
-// [0, pi/2), folded to [0, pi/4] by the complement, and summed by its Taylor
-// series (13 terms: truncation below 1e-25 there).
-__host__ __device__ constexpr double ct_sin_series(double x) {
-    double term = x, sum = x;
-    for (int i = 1; i <= 12; ++i) {
-        term *= -x * x / ((2.0 * i) * (2.0 * i + 1.0));
-        sum += term;
-    }
-    return sum;
+// [0, pi/4] (folded by the complement) and summed by its Taylor series in
+// double-double arithmetic (Dekker's error-free sum and product; 14 terms,
+// truncation below 1e-30), then rounded once: the constants carry no error of
+// their own beyond the final rounding, in either precision.
+struct CtDd {
+    double h, l;
+};
+constexpr CtDd ct_fast2(double a, double b) {
+    const double s = a + b;
+    return CtDd{s, b - (s - a)};
 }
-__host__ __device__ constexpr double ct_cos_series(double x) {
-    double term = 1.0, sum = 1.0;
-    for (int i = 1; i <= 12; ++i) {
-        term *= -x * x / ((2.0 * i - 1.0) * (2.0 * i));
-        sum += term;
-    }
-    return sum;
+constexpr CtDd ct_add(CtDd a, CtDd b) {
+    const double s = a.h + b.h, t = s - a.h;
+    const double e = (a.h - (s - t)) + (b.h - t);
+    return ct_fast2(s, e + (a.l + b.l));
 }
-__host__ __device__ constexpr double ct_trig(int m, int n, bool want_sin) {
+constexpr CtDd ct_mul(CtDd a, CtDd b) {
+    const double p = a.h * b.h;
+    const double ca = 134217729.0 * a.h, ah = ca - (ca - a.h), al = a.h - ah;
+    const double cb = 134217729.0 * b.h, bh = cb - (cb - b.h), bl = b.h - bh;
+    const double e = ((ah * bh - p) + ah * bl + al * bh) + al * bl;
+    return ct_fast2(p, e + (a.h * b.l + a.l * b.h));
+}
+constexpr CtDd ct_div(CtDd a, double d) {  // two quotient digits
+    const double q = a.h / d;
+    const CtDd r = ct_add(a, ct_mul(CtDd{-q, 0.0}, CtDd{d, 0.0}));
+    return ct_fast2(q, (r.h + r.l) / d);
+}
+constexpr double ct_trig(int m, int n, bool want_sin) {
     const long long r = ((long long)m % n + n) % n;
     const long long q = (4 * r) / n;     // quarter turns
     const long long rr = 4 * r - q * n;  // rest: (pi / 2) rr / n
     const bool flip = 2 * rr > n;
-    const double x = 1.57079632679489661923 * (double)(flip ? n - rr : rr) / (double)n;
-    const double s0 = flip ? ct_cos_series(x) : ct_sin_series(x);
-    const double c0 = flip ? ct_sin_series(x) : ct_cos_series(x);
+    const CtDd half_pi{1.5707963267948966, 6.123233995736766e-17};
+    const CtDd x = ct_div(ct_mul(half_pi, CtDd{(double)(flip ? n - rr : rr), 0.0}), (double)n);
+    const CtDd x2 = ct_mul(x, x), mx2{-x2.h, -x2.l};
+    CtDd ts = x, ss = x, tc{1.0, 0.0}, sc{1.0, 0.0};
+    for (int i = 1; i <= 14; ++i) {
+        ts = ct_div(ct_mul(ts, mx2), (2.0 * i) * (2.0 * i + 1.0));
+        tc = ct_div(ct_mul(tc, mx2), (2.0 * i - 1.0) * (2.0 * i));
+        ss = ct_add(ss, ts);
+        sc = ct_add(sc, tc);
+    }
+    const double s0 = flip ? sc.h : ss.h, c0 = flip ? ss.h : sc.h;
     const double c = q == 0 ? c0 : q == 1 ? -s0 : q == 2 ? -c0 : s0;
     const double s = q == 0 ? s0 : q == 1 ? c0 : q == 2 ? -s0 : -c0;
     return want_sin ? s : c;
 }
+template <int N>
+struct CtTable {  // cos and sin of 2 pi m / N, m < N
+    double c[N], s[N];
+    constexpr CtTable() : c(), s() {
+        for (int m = 0; m < N; ++m) c[m] = ct_trig(m, N, false), s[m] = ct_trig(m, N, true);
+    }
+};
+template <int N>
+struct CtTrig {
+    static constexpr CtTable<N> t{};
+};
 
-// ---- in-register DFT of any 7-smooth size (natural order in and out) ----------
+// ---- in-register forward DFT of any 7-smooth size (natural order in and out) ---
 // Sizes 2, 3, 4, 5, 7, 8, 16 use the fixed kernels; any other N = A B runs B
 // DFTs of size A over x[B n1 + n2], twiddles by W_N^{n2 k1}, and A DFTs of size
-// B, output k1 + A k2.
+// B, output k1 + A k2.  Backward passes conjugate their inputs and outputs.
 template <int N>
 struct MrSplit {
     static constexpr int A = (N % 16 == 0 && N > 16) ? 16
@@ -78,33 +123,34 @@ struct MrSplit {
     static constexpr int B = N / A;
 };
 
-template <int N, int DIR>
+template <typename T, int N>
 struct DftMR {
-    __device__ __forceinline__ static void run(cx<float> *v) {
+    __device__ __forceinline__ static void run(cx<T> *v) {
         if constexpr (N == 1) {
         } else if constexpr (N == 2 || N == 3 || N == 4 || N == 5 || N == 7 || N == 8 || N == 16) {
-            Dft<float, N, DIR>::run(v);
+            Dft<T, N, -1>::run(v);
         } else {
             constexpr int A = MrSplit<N>::A, B = MrSplit<N>::B;
             static_assert(A * B == N && B > 1, "size must be 7-smooth");
-            cx<float> t[B][A];
+            constexpr CtTable<N> tab = CtTrig<N>::t;
+            cx<T> t[B][A];
 #pragma unroll
             for (int n2 = 0; n2 < B; ++n2) {
 #pragma unroll
                 for (int n1 = 0; n1 < A; ++n1) t[n2][n1] = v[B * n1 + n2];
-                DftMR<A, DIR>::run(t[n2]);
+                DftMR<T, A>::run(t[n2]);
             }
 #pragma unroll
             for (int n2 = 1; n2 < B; ++n2)
 #pragma unroll
                 for (int k1 = 1; k1 < A; ++k1)
-                    t[n2][k1] = crot<DIR>(t[n2][k1], (float)ct_trig(n2 * k1, N, false), (float)ct_trig(n2 * k1, N, true));
+                    t[n2][k1] = crot<-1>(t[n2][k1], (T)tab.c[(n2 * k1) % N], (T)tab.s[(n2 * k1) % N]);
 #pragma unroll
             for (int k1 = 0; k1 < A; ++k1) {
-                cx<float> u[B];
+                cx<T> u[B];
 #pragma unroll
                 for (int n2 = 0; n2 < B; ++n2) u[n2] = t[n2][k1];
-                DftMR<B, DIR>::run(u);
+                DftMR<T, B>::run(u);
 #pragma unroll
                 for (int k2 = 0; k2 < B; ++k2) v[k1 + A * k2] = u[k2];
             }
@@ -113,315 +159,365 @@ struct DftMR {
 };
 
 // ---- tile geometry -----------------------------------------------------------
-#ifndef PF_MR_SPZ_RES
-#define PF_MR_SPZ_RES 2
+// Exchange tiles above this many bytes go through LDS in two halves: up to 80
+// KB two workgroups still fit on a CU, and the halves' two more barriers cost
+// more than a third workgroup brings (FP32 Y pass, whole against halves: 384
+// points, 50 KB, 5.14 against 4.64 TB/s; 500 points, 64 KB, 4.84 against 4.68;
+// 600 points, 77 KB, 4.83 against 4.89 and its Z passes 4.11 / 4.26 against
+// 3.97 / 4.15).  Longer tiles fit one workgroup only when whole.
+#ifndef PF_MR_SPLIT_ABOVE
+#define PF_MR_SPLIT_ABOVE 81920
 #endif
-// X kernels: line pairs per tile (a power of two; the lines' workspace rows are
-// separate, so the tile width does not change the row accesses)
-#ifndef PF_MR_XP
-#define PF_MR_XP 4
-#endif
-// C2C kernel: two step-1 items per thread for strongly unbalanced factor pairs
-#ifndef PF_MR_HALF
-#define PF_MR_HALF 1
-#endif
-// global accesses with the nontemporal hint: bit 0 stores, bit 1 loads
-#ifndef PF_MR_NT
-#define PF_MR_NT 0
-#endif
-typedef float mr_f2 __attribute__((ext_vector_type(2)));
-__device__ __forceinline__ float2 mr_ld(const float2 *p) {
-    if constexpr ((PF_MR_NT & 2) != 0) {
-        const mr_f2 u = __builtin_nontemporal_load(reinterpret_cast<const mr_f2 *>(p));
-        return make_float2(u.x, u.y);
-    } else {
-        return *p;
-    }
-}
-__device__ __forceinline__ float mr_ld(const float *p) {
-    if constexpr ((PF_MR_NT & 2) != 0) return __builtin_nontemporal_load(p);
-    else return *p;
-}
-__device__ __forceinline__ void mr_st(float2 *p, float2 v) {
-    if constexpr ((PF_MR_NT & 1) != 0) {
-        const mr_f2 u = {v.x, v.y};
-        __builtin_nontemporal_store(u, reinterpret_cast<mr_f2 *>(p));
-    } else {
-        *p = v;
-    }
-}
-__device__ __forceinline__ void mr_st(float *p, float v) {
-    if constexpr ((PF_MR_NT & 1) != 0) __builtin_nontemporal_store(v, p);
-    else *p = v;
-}
 
-__host__ __device__ constexpr int mr_threads(int n1, int n2) {
-    return 16 * (((n1 > n2 ? n1 : n2) + 3) / 4 * 4);  // 16 columns x max(N1, N2) items, whole waves
+// columns of one C2C tile: a 128-byte workspace row
+template <typename T>
+__host__ __device__ constexpr int mr_cols() {
+    return 128 / (int)sizeof(cx<T>);
 }
-// Threads per column of the C2C kernel: max(N1, N2) rounded up to 4, or, where
-// N2 >= 2 N1 and N2 >= 24, max(N1, ceil(N2 / 2)) with up to two step-1 items
-// per thread -- smaller workgroups, of which more fit on a CU, where step 2
-// would leave most threads idle.  Measured per length on the Y pass: faster
-// for N2 of 25 and more (lengths 125, 175, 243, 250; 245 even), slower by
-// 4-8% for N2 of 21 and less.
+// Threads per column of the C2C kernel: max(N1, N2) rounded up to whole waves
+// (one step-1 item per thread; two items in half the threads measured slower
+// where N2 >= 2 N1: FP64 length 250 = 10 x 25, forward Z pass 81 against 71 us
+// at 300 x 280 x 250)
+template <typename T>
 __host__ __device__ constexpr int mr_c2c_cols(int n1, int n2) {
-    const int full = ((n1 > n2 ? n1 : n2) + 3) / 4 * 4;
-    const int half2 = (n2 + 1) / 2;
-    const int half = ((n1 > half2 ? n1 : half2) + 3) / 4 * 4;
-    return PF_MR_HALF && n2 >= 2 * n1 && n2 >= 24 && half < full ? half : full;
+    const int w = 64 / mr_cols<T>();
+    return ((n1 > n2 ? n1 : n2) + w - 1) / w * w;
 }
-__host__ __device__ constexpr int mr_c2c_threads(int n1, int n2) { return 16 * mr_c2c_cols(n1, n2); }
-// X kernels: PF_MR_XP pairs x max(N1, N2) items, whole waves
+template <typename T>
+__host__ __device__ constexpr int mr_c2c_threads(int n1, int n2) {
+    return mr_cols<T>() * mr_c2c_cols<T>(n1, n2);
+}
+// X kernels: line pairs per tile (a power of two; the lines' workspace rows
+// are separate, so the tile width does not change the row accesses): 4, more
+// where 4 pairs' step-1 items would not fill a wave, 2 where the tile would
+// exceed 40 KB (FP64 lengths above 640; fewer than 4 workgroups per CU)
+template <typename T>
+__host__ __device__ constexpr int mr_xp(int n1, int n2) {
+    const int xp = n2 >= 16 ? 4 : n2 >= 8 ? 8 : 16;
+    return xp == 4 && 4 * n1 * n2 * (int)sizeof(cx<T>) > 40960 ? 2 : xp;
+}
+// X kernels: pairs x max(N1, N2) items, whole waves
+template <typename T>
 __host__ __device__ constexpr int mr_x_threads(int n1, int n2) {
-    return (PF_MR_XP * (n1 > n2 ? n1 : n2) + 63) / 64 * 64;
+    return (mr_xp<T>(n1, n2) * (n1 > n2 ? n1 : n2) + 63) / 64 * 64;
 }
 
-template <int N1, int N2>
+template <typename T, int N1, int N2>
 struct MrShape {
     static constexpr int N = N1 * N2;
-    static constexpr int NQ = N1 > N2 ? N1 : N2;
-    static constexpr int THREADS = mr_threads(N1, N2);
-    // exchange tile: row (c, k1) or (k1, c) of P2 entries, P2 odd so that the
+    static constexpr int C = mr_cols<T>();
+    // exchange tile: row (k1, q) or (c, k1) of P2 entries, P2 odd so that the
     // step-2 reads of consecutive rows fall on different banks
     static constexpr int P2 = N2 % 2 == 0 ? N2 + 1 : N2;
-    static constexpr int XCH = 16 * N1 * P2;
+    static constexpr bool SPLIT = 128 * N1 * P2 > PF_MR_SPLIT_ABOVE;
     // X passes: XP line pairs per tile, XTHREADS threads; one complex line per
     // pair at pitch SP (= 16 mod 32, >= N)
-    static constexpr int XP = PF_MR_XP;
-    static constexpr int XTHREADS = mr_x_threads(N1, N2);
+    static constexpr int XP = mr_xp<T>(N1, N2);
+    static constexpr int XTHREADS = mr_x_threads<T>(N1, N2);
     static constexpr int SP = N + ((16 - N % 32) % 32 + 32) % 32;
-    static constexpr int XLDS = XP * N1 * P2 > XP * SP ? XP * N1 * P2 : XP * SP;
-    // C2C pass with a line side: line-major tile copy at pitch SPZ (= PF_MR_SPZ_RES
-    // mod 32, >= N), written and read by lanes along the columns
-    static constexpr int SPZ = N + ((PF_MR_SPZ_RES - N % 32) % 32 + 32) % 32;
-    static constexpr int CLDS = XCH > 16 * SPZ ? XCH : 16 * SPZ;
-    // C2C kernel: threads per column, threads, step-1 items per thread
-    static constexpr int CT = mr_c2c_cols(N1, N2);
-    static constexpr int CTHREADS = 16 * CT;
-    static constexpr int I1 = (N2 + CT - 1) / CT;
+    static constexpr int XLDS = (XP * N1 * P2 > XP * SP ? XP * N1 * P2 : XP * SP) * (int)sizeof(cx<T>);
+    // C2C pass with a line side: line-major tile copy at pitch SPZ >= N, written
+    // by lanes along the points and read by lanes along the columns (C columns x
+    // 64 / C points per wave): the residue gives the reads of one LDS cycle (256
+    // bytes, E elements) distinct banks
+    static constexpr int E = 256 / (SPLIT ? (int)sizeof(T) : (int)sizeof(cx<T>)), SPR = E / C;
+    static constexpr int SPZ = N + ((SPR - N % E) % E + E) % E;
+    static constexpr int XCHB = 128 * N1 * P2 / (SPLIT ? 2 : 1);
+    static constexpr int SPZB = C * SPZ * (int)sizeof(cx<T>) / (SPLIT ? 2 : 1);
+    static constexpr int CLDS = XCHB > SPZB ? XCHB : SPZB;
+    // C2C kernel: threads
+    static constexpr int CTHREADS = mr_c2c_threads<T>(N1, N2);
 };
+
+// ---- global accesses -------------------------------------------------------------
+// Through pointers qualified as global memory: the kernels take their pointers
+// from the plan's arguments or from a batch's table, so the compiler cannot tell
+// that they are not LDS, and unqualified ones become flat accesses, which also
+// take the LDS path and its wait counter.
+#define PF_GLOBAL __attribute__((address_space(1)))
+template <typename T>
+__device__ __forceinline__ cx<T> mr_ld(const cx<T> *p) {
+    typedef T v2 __attribute__((ext_vector_type(2)));
+    const v2 u = *(const PF_GLOBAL v2 *)p;
+    return cmk<T>(u.x, u.y);
+}
+template <typename T>
+__device__ __forceinline__ T mr_ld1(const T *p) {
+    return *(const PF_GLOBAL T *)p;
+}
+template <typename T>
+__device__ __forceinline__ void mr_st(cx<T> *p, cx<T> v) {
+    typedef T v2 __attribute__((ext_vector_type(2)));
+    const v2 u = {v.x, v.y};
+    *(PF_GLOBAL v2 *)p = u;
+}
+template <typename T>
+__device__ __forceinline__ void mr_st1(T *p, T v) {
+    *(PF_GLOBAL T *)p = v;
+}
 
 // ---- C2C column tile -----------------------------------------------------------
+template <typename T>
 struct MrC2C {
-    const cx<float> *in;
-    cx<float> *out;
-    const cx<float> *tw;  // W_N^m, m < N (forward sign)
+    const cx<T> *in;
+    cx<T> *out;
+    const cx<T> *tw;  // W_N^m, m < N (forward sign)
     long long ib, isc, isp, ob, osc, osp;
     int ncol;
+    T sgn;  // +1 forward, -1 backward (the sign of the imaginary parts)
 };
 
+template <int C>
 __device__ __forceinline__ long long mr_side_base(const Side &s, long long a, int cb) {
     const int cpb = (int)s.cpb;
     const int blk = cb / cpb;
-    return a * s.sa + (long long)blk * s.sblk + (long long)((cb - blk * cpb) * 16) * s.sc;
+    return a * s.sa + (long long)blk * s.sblk + (long long)((cb - blk * cpb) * C) * s.sc;
 }
 
-// tile `tile` of the C2C pass a (16 columns per tile), reading inp, writing outp
-__device__ __forceinline__ MrC2C mr_c2c_args(const PassArgs &a, const void *inp, void *outp, long long tile) {
-    MrC2C t;
+// tile `tile` of the C2C pass a, reading inp, writing outp
+template <typename T>
+__device__ __forceinline__ MrC2C<T> mr_c2c_args(const PassArgs &a, int dir, const void *inp, void *outp,
+                                                long long tile) {
+    constexpr int C = mr_cols<T>();
+    MrC2C<T> t;
     // tile order 1 walks the outer index fastest (neighbouring tiles then touch
     // adjacent rows and lines of sides whose column blocks lie far apart)
     const int CB = (int)a.CB, A = (int)a.A;
     const int ta = a.tile_order ? (int)tile % A : (int)tile / CB;
     const int cb = a.tile_order ? (int)tile / A : (int)tile - ta * CB;
-    t.in = reinterpret_cast<const cx<float> *>(inp);
-    t.out = reinterpret_cast<cx<float> *>(outp);
-    t.tw = reinterpret_cast<const cx<float> *>(a.tw);
-    t.ib = mr_side_base(a.in_s, ta, cb);
-    t.ob = mr_side_base(a.out_s, ta, cb);
+    t.in = reinterpret_cast<const cx<T> *>(inp);
+    t.out = reinterpret_cast<cx<T> *>(outp);
+    t.tw = reinterpret_cast<const cx<T> *>(a.tw);
+    t.ib = mr_side_base<C>(a.in_s, ta, cb);
+    t.ob = mr_side_base<C>(a.out_s, ta, cb);
     t.isc = a.in_s.sc, t.isp = a.in_s.sp, t.osc = a.out_s.sc, t.osp = a.out_s.sp;
-    const int left = a.C - cb * 16;
-    t.ncol = left < 16 ? left : 16;
+    const int left = a.C - cb * C;
+    t.ncol = left < C ? left : C;
+    t.sgn = dir < 0 ? T(1) : T(-1);
     return t;
 }
 
-template <int N1, int N2, int DIR>
-__device__ __forceinline__ void mr_c2c_body(const MrC2C &t) {
-    using S = MrShape<N1, N2>;
-    constexpr int N = S::N;
+// ---- a trip through LDS ---------------------------------------------------------
+// One step's values travel between threads: every thread puts its values,
+// synchronises, and gets its new ones -- whole complex values, or (SPLIT) the
+// real parts and then the imaginary parts through the same words.  put(w) /
+// get(g) call w(slot, value) / g(slot, value) for each of the thread's values.
+// Ends with the reads; the caller synchronises before LDS is written again.
+template <typename T, bool SPLIT, typename PUT, typename GET>
+__device__ __forceinline__ void mr_trip(PUT put, GET get) {
+    if constexpr (SPLIT) {
+        T *lds = reinterpret_cast<T *>(pf_smem);
+        put([&](int i, const cx<T> &v) { lds[i] = v.x; });
+        __syncthreads();
+        get([&](int i, cx<T> &v) { v.x = lds[i]; });
+        __syncthreads();
+        put([&](int i, const cx<T> &v) { lds[i] = v.y; });
+        __syncthreads();
+        get([&](int i, cx<T> &v) { v.y = lds[i]; });
+    } else {
+        cx<T> *lds = reinterpret_cast<cx<T> *>(pf_smem);
+        put([&](int i, const cx<T> &v) { lds[i] = v; });
+        __syncthreads();
+        get([&](int i, cx<T> &v) { v = lds[i]; });
+    }
+}
+
+template <typename T, int N1, int N2>
+__device__ __forceinline__ void mr_c2c_body(const MrC2C<T> &t) {
+    using S = MrShape<T, N1, N2>;
+    constexpr int N = S::N, C = S::C;
     constexpr int NT = S::CTHREADS;
-    constexpr int ITEMS = (16 * N + NT - 1) / NT;  // tile points per thread
-    cx<float> *lds = reinterpret_cast<cx<float> *>(pf_smem);
+    constexpr int ITEMS = (C * N + NT - 1) / NT;  // tile points per thread
     const int tid = threadIdx.x;
-    const int c = tid & 15, j = tid >> 4;
+    const int c = tid & (C - 1), j = tid / C;
     const bool cv = c < t.ncol;
     // a side whose columns are whole lines (points contiguous) goes through a
     // line-major LDS copy of the tile, so that its global accesses run along
     // the points; a row side is read / written by the step-1 / step-2 threads
     const bool in_lines = t.isp == 1 && t.isc != 1;
     const bool out_lines = t.osp == 1 && t.osc != 1;
+    // step 1, item q = j: the N1 points q + N2 m of column c (arrays zeroed
+    // before conditional fills: the compiler otherwise keeps FP64 ones in scratch
+    // memory)
+    cx<T> x[N1];
+#pragma unroll
+    for (int m = 0; m < N1; ++m) x[m] = cmk<T>(T(0), T(0));
     if (in_lines) {
-        cx<float> r[ITEMS];
+        cx<T> r[ITEMS];
 #pragma unroll
         for (int i = 0; i < ITEMS; ++i) {
             const int f = tid + i * NT;
             const int cc = f / N, p = f - cc * N;
-            r[i] = make_float2(0.f, 0.f);
-            if (f < 16 * N && cc < t.ncol) r[i] = mr_ld(t.in + t.ib + cc * t.isc + p);
+            r[i] = cmk<T>(T(0), T(0));
+            if (f < C * N && cc < t.ncol) r[i] = mr_ld<T>(t.in + t.ib + cc * t.isc + p);
         }
+        mr_trip<T, S::SPLIT>(
+            [&](auto w) {
 #pragma unroll
-        for (int i = 0; i < ITEMS; ++i) {
-            const int f = tid + i * NT;
-            const int cc = f / N, p = f - cc * N;
-            if (f < 16 * N) lds[cc * S::SPZ + p] = r[i];
-        }
-        __syncthreads();
+                for (int i = 0; i < ITEMS; ++i) {
+                    const int f = tid + i * NT;
+                    const int cc = f / N, p = f - cc * N;
+                    if (f < C * N) w(cc * S::SPZ + p, r[i]);
+                }
+            },
+            [&](auto g) {
+                if (j < N2) {
+#pragma unroll
+                    for (int m = 0; m < N1; ++m) g(c * S::SPZ + j + N2 * m, x[m]);
+                }
+            });
+    } else if (j < N2 && cv) {
+        const cx<T> *src = t.in + t.ib + c * t.isc + j * t.isp;
+        const long long step = (long long)N2 * t.isp;
+#pragma unroll
+        for (int m = 0; m < N1; ++m) x[m] = mr_ld<T>(src + m * step);
     }
-    // step 1, items q = j + it CT (it < I1): the N1 points q + N2 m of column c;
-    // every item's loads are issued before the first transform
-    cx<float> x[S::I1][N1];
+    if (j < N2) {
 #pragma unroll
-    for (int it = 0; it < S::I1; ++it) {
-        const int q = j + it * S::CT;
+        for (int m = 0; m < N1; ++m) x[m].y *= t.sgn;
+        DftMR<T, N1>::run(x);
 #pragma unroll
-        for (int m = 0; m < N1; ++m) x[it][m] = make_float2(0.f, 0.f);
-        if (q < N2) {
-            if (in_lines) {
-#pragma unroll
-                for (int m = 0; m < N1; ++m) x[it][m] = lds[c * S::SPZ + q + N2 * m];
-            } else if (cv) {
-                const cx<float> *src = t.in + t.ib + c * t.isc + q * t.isp;
-                const long long step = (long long)N2 * t.isp;
-#pragma unroll
-                for (int m = 0; m < N1; ++m) x[it][m] = mr_ld(src + m * step);
-            }
-        }
-    }
-#pragma unroll
-    for (int it = 0; it < S::I1; ++it) {
-        const int q = j + it * S::CT;
-        if (q < N2) {
-            DftMR<N1, DIR>::run(x[it]);
-#pragma unroll
-            for (int k1 = 1; k1 < N1; ++k1) {
-                cx<float> w = t.tw[q * k1];
-                if (DIR > 0) w.y = -w.y;
-                x[it][k1] = cmul(x[it][k1], w);
-            }
-        }
+        for (int k1 = 1; k1 < N1; ++k1) x[k1] = cmul(x[k1], mr_ld<T>(t.tw + j * k1));
     }
     if (in_lines) __syncthreads();  // the staged lines are read before the exchange tile overwrites them
+    cx<T> y[N2];
 #pragma unroll
-    for (int it = 0; it < S::I1; ++it) {
-        const int q = j + it * S::CT;
-        if (q < N2) {
+    for (int n2 = 0; n2 < N2; ++n2) y[n2] = cmk<T>(T(0), T(0));
+    mr_trip<T, S::SPLIT>(
+        [&](auto w) {
+            if (j < N2) {
 #pragma unroll
-            for (int k1 = 0; k1 < N1; ++k1) lds[(k1 * S::P2 + q) * 16 + c] = x[it][k1];
-        }
-    }
-    __syncthreads();
-    cx<float> y[N2];
+                for (int k1 = 0; k1 < N1; ++k1) w((k1 * S::P2 + j) * C + c, x[k1]);
+            }
+        },
+        [&](auto g) {
+            if (j < N1) {
+#pragma unroll
+                for (int n2 = 0; n2 < N2; ++n2) g((j * S::P2 + n2) * C + c, y[n2]);
+            }
+        });
     if (j < N1) {  // step 2, item k1 = j: outputs k1 + N1 k2 of column c
+        DftMR<T, N2>::run(y);
 #pragma unroll
-        for (int n2 = 0; n2 < N2; ++n2) y[n2] = lds[(j * S::P2 + n2) * 16 + c];
-        DftMR<N2, DIR>::run(y);
+        for (int k2 = 0; k2 < N2; ++k2) y[k2].y *= t.sgn;
     }
     if (out_lines) {
         __syncthreads();  // the exchange tile is read before the line-major copy overwrites it
-        if (j < N1) {
+        cx<T> r[ITEMS];
 #pragma unroll
-            for (int k2 = 0; k2 < N2; ++k2) lds[c * S::SPZ + j + N1 * k2] = y[k2];
-        }
-        __syncthreads();
-        cx<float> r[ITEMS];
+        for (int i = 0; i < ITEMS; ++i) r[i] = cmk<T>(T(0), T(0));
+        mr_trip<T, S::SPLIT>(
+            [&](auto w) {
+                if (j < N1) {
+#pragma unroll
+                    for (int k2 = 0; k2 < N2; ++k2) w(c * S::SPZ + j + N1 * k2, y[k2]);
+                }
+            },
+            [&](auto g) {
+#pragma unroll
+                for (int i = 0; i < ITEMS; ++i) {
+                    const int f = tid + i * NT;
+                    const int cc = f / N, p = f - cc * N;
+                    if (f < C * N) g(cc * S::SPZ + p, r[i]);
+                }
+            });
 #pragma unroll
         for (int i = 0; i < ITEMS; ++i) {
             const int f = tid + i * NT;
             const int cc = f / N, p = f - cc * N;
-            if (f < 16 * N) r[i] = lds[cc * S::SPZ + p];
-        }
-#pragma unroll
-        for (int i = 0; i < ITEMS; ++i) {
-            const int f = tid + i * NT;
-            const int cc = f / N, p = f - cc * N;
-            if (f < 16 * N && cc < t.ncol) mr_st(t.out + t.ob + cc * t.osc + p, r[i]);
+            if (f < C * N && cc < t.ncol) mr_st<T>(t.out + t.ob + cc * t.osc + p, r[i]);
         }
     } else if (j < N1 && cv) {
-        cx<float> *dst = t.out + t.ob + c * t.osc + j * t.osp;
+        cx<T> *dst = t.out + t.ob + c * t.osc + j * t.osp;
         const long long step = (long long)N1 * t.osp;
 #pragma unroll
-        for (int k2 = 0; k2 < N2; ++k2) mr_st(dst + k2 * step, y[k2]);
+        for (int k2 = 0; k2 < N2; ++k2) mr_st<T>(dst + k2 * step, y[k2]);
     }
 }
 
-// ---- X passes: PF_MR_XP pairs of real lines per tile ----------------------------
+// ---- X passes: XP pairs of real lines per tile ----------------------------------
+template <typename T>
 struct MrX {
-    const void *in;
-    void *out;
-    const cx<float> *tw;  // W_N^m, m < N = nx (forward sign)
+    const T *in_r;       // forward input
+    const cx<T> *in_c;   // backward input
+    T *out_r;            // backward output
+    cx<T> *out_c;        // forward output
+    const cx<T> *tw;     // W_N^m, m < N = nx (forward sign)
     long long g0, lines, ld_real, ny, zrows, kbstride;
     int y0, nkb, nxh;
 };
 
-__device__ __forceinline__ MrX mr_x_args(const PassArgs &a, const void *inp, void *outp, long long tile) {
-    MrX t;
-    t.in = inp;
-    t.out = outp;
-    t.tw = reinterpret_cast<const cx<float> *>(a.tw);
-    t.g0 = tile * (2 * PF_MR_XP);
+template <typename T>
+__device__ __forceinline__ MrX<T> mr_x_args(const PassArgs &a, const void *inp, void *outp, long long tile, int xp) {
+    MrX<T> t;
+    t.in_r = reinterpret_cast<const T *>(inp);
+    t.in_c = reinterpret_cast<const cx<T> *>(inp);
+    t.out_r = reinterpret_cast<T *>(outp);
+    t.out_c = reinterpret_cast<cx<T> *>(outp);
+    t.tw = reinterpret_cast<const cx<T> *>(a.tw);
+    t.g0 = tile * (2 * xp);
     t.lines = a.lines;
     t.ld_real = a.ld_real;
     t.ny = a.ny;
     t.zrows = a.zrows;
-    t.kbstride = a.kbrows << 4;
+    t.kbstride = a.kbrows * mr_cols<T>();
     t.y0 = a.y0;
     t.nkb = a.nkb;
     t.nxh = a.nxh;
     return t;
 }
 
-// row offset (workspace, column block 0) of the 2 PF_MR_XP lines of the tile:
+// row offset (workspace, column block 0) of the 2 XP lines of the tile:
 // line g = z ny + y starts at row z zrows + y0 + y
-__device__ __forceinline__ void mr_rowoff(const MrX &t, long long *rowoff) {
+template <typename T, int XP>
+__device__ __forceinline__ void mr_rowoff(const MrX<T> &t, long long *rowoff) {
     const int tid = threadIdx.x;
-    if (tid < 2 * PF_MR_XP) {
+    if (tid < 2 * XP) {
         const long long g = t.g0 + tid;
         const long long z = g / t.ny;
         const long long y = g - z * t.ny;
-        rowoff[tid] = (z * t.zrows + t.y0 + y) << 4;
+        rowoff[tid] = (z * t.zrows + t.y0 + y) * mr_cols<T>();
     }
 }
 
 // forward: real lines -> half spectra in the blocked workspace
-template <int N1, int N2>
-__device__ __forceinline__ void mr_r2c_body(const MrX &t) {
-    using S = MrShape<N1, N2>;
-    constexpr int N = S::N;
-    __shared__ long long rowoff[2 * PF_MR_XP];
-    cx<float> *lds = reinterpret_cast<cx<float> *>(pf_smem);
+template <typename T, int N1, int N2>
+__device__ __forceinline__ void mr_r2c_body(const MrX<T> &t) {
+    using S = MrShape<T, N1, N2>;
+    constexpr int N = S::N, C = S::C;
+    __shared__ long long rowoff[2 * S::XP];
+    cx<T> *lds = reinterpret_cast<cx<T> *>(pf_smem);
     const int tid = threadIdx.x;
-    mr_rowoff(t, rowoff);
-    const float *__restrict__ in = reinterpret_cast<const float *>(t.in);
-    cx<float> *__restrict__ out = reinterpret_cast<cx<float> *>(t.out);
+    mr_rowoff<T, S::XP>(t, rowoff);
     if (tid < S::XP * N2) {  // step 1, item (c, q): lanes along the points of the lines
         const int c = tid / N2, q = tid - c * N2;
         const long long ga = t.g0 + 2 * c;
-        cx<float> x[N1];
+        cx<T> x[N1];
 #pragma unroll
-        for (int m = 0; m < N1; ++m) x[m] = make_float2(0.f, 0.f);
+        for (int m = 0; m < N1; ++m) x[m] = cmk<T>(T(0), T(0));
         if (ga < t.lines) {
-            const float *pa = in + ga * t.ld_real + q;
+            const T *pa = t.in_r + ga * t.ld_real + q;
 #pragma unroll
-            for (int m = 0; m < N1; ++m) x[m].x = mr_ld(pa + N2 * m);
+            for (int m = 0; m < N1; ++m) x[m].x = mr_ld1(pa + N2 * m);
         }
         if (ga + 1 < t.lines) {
-            const float *pb = in + (ga + 1) * t.ld_real + q;
+            const T *pb = t.in_r + (ga + 1) * t.ld_real + q;
 #pragma unroll
-            for (int m = 0; m < N1; ++m) x[m].y = mr_ld(pb + N2 * m);
+            for (int m = 0; m < N1; ++m) x[m].y = mr_ld1(pb + N2 * m);
         }
-        DftMR<N1, -1>::run(x);
+        DftMR<T, N1>::run(x);
 #pragma unroll
-        for (int k1 = 1; k1 < N1; ++k1) x[k1] = cmul(x[k1], t.tw[q * k1]);
+        for (int k1 = 1; k1 < N1; ++k1) x[k1] = cmul(x[k1], mr_ld<T>(t.tw + q * k1));
 #pragma unroll
         for (int k1 = 0; k1 < N1; ++k1) lds[(c * N1 + k1) * S::P2 + q] = x[k1];
     }
     __syncthreads();
-    cx<float> y[N2];
+    cx<T> y[N2];
     const int c2 = tid / N1, k1 = tid - c2 * N1;
     if (tid < S::XP * N1) {  // step 2, item (c, k1)
 #pragma unroll
         for (int n2 = 0; n2 < N2; ++n2) y[n2] = lds[(c2 * N1 + k1) * S::P2 + n2];
-        DftMR<N2, -1>::run(y);
+        DftMR<T, N2>::run(y);
     }
     __syncthreads();  // the exchange tile is read before the spectra overwrite it
     if (tid < S::XP * N1) {
@@ -430,83 +526,80 @@ __device__ __forceinline__ void mr_r2c_body(const MrX &t) {
     }
     __syncthreads();
     // split Z = A + i B into the half spectra of the two lines, row by row:
-    // mode (kb, cc, kk), lanes along the 16 modes of a row
-    const int total = t.nkb * 16 * S::XP;
+    // mode (kb, cc, kk), lanes along the C modes of a row
+    const int total = t.nkb * C * S::XP;
+    const T h = T(0.5);
     for (int f = tid; f < total; f += S::XTHREADS) {
-        const int kk = f & 15, cc = (f >> 4) & (S::XP - 1), kb = f / (16 * S::XP);
-        const int k = kb * 16 + kk;
+        const int kk = f & (C - 1), cc = (f / C) & (S::XP - 1), kb = f / (C * S::XP);
+        const int k = kb * C + kk;
         const long long ga = t.g0 + 2 * cc;
         if (k < t.nxh && ga < t.lines) {
-            const cx<float> z = lds[cc * S::SP + k];
-            const cx<float> w = lds[cc * S::SP + (k == 0 ? 0 : N - k)];
+            const cx<T> z = lds[cc * S::SP + k];
+            const cx<T> w = lds[cc * S::SP + (k == 0 ? 0 : N - k)];
             const long long o = kb * t.kbstride + kk;
-            mr_st(out + rowoff[2 * cc] + o, make_float2((z.x + w.x) * 0.5f, (z.y - w.y) * 0.5f));
-            if (ga + 1 < t.lines) mr_st(out + rowoff[2 * cc + 1] + o, make_float2((z.y + w.y) * 0.5f, (w.x - z.x) * 0.5f));
+            mr_st<T>(t.out_c + rowoff[2 * cc] + o, cmk<T>((z.x + w.x) * h, (z.y - w.y) * h));
+            if (ga + 1 < t.lines)
+                mr_st<T>(t.out_c + rowoff[2 * cc + 1] + o, cmk<T>((z.y + w.y) * h, (w.x - z.x) * h));
         }
     }
 }
 
 // backward: half spectra in the blocked workspace -> real lines
-template <int N1, int N2>
-__device__ __forceinline__ void mr_c2r_body(const MrX &t) {
-    using S = MrShape<N1, N2>;
-    constexpr int N = S::N;
+template <typename T, int N1, int N2>
+__device__ __forceinline__ void mr_c2r_body(const MrX<T> &t) {
+    using S = MrShape<T, N1, N2>;
+    constexpr int N = S::N, C = S::C;
     constexpr int EH = 4;  // rows in flight per thread before the LDS writes
-    __shared__ long long rowoff[2 * PF_MR_XP];
-    cx<float> *lds = reinterpret_cast<cx<float> *>(pf_smem);
+    __shared__ long long rowoff[2 * S::XP];
+    cx<T> *lds = reinterpret_cast<cx<T> *>(pf_smem);
     const int tid = threadIdx.x;
-    mr_rowoff(t, rowoff);
+    mr_rowoff<T, S::XP>(t, rowoff);
     __syncthreads();
-    const cx<float> *__restrict__ in = reinterpret_cast<const cx<float> *>(t.in);
-    float *__restrict__ out = reinterpret_cast<float *>(t.out);
-    // Z = A + i B on the whole line: modes k < nxh from the rows, the rest by
-    // Hermitian symmetry; the imaginary parts of modes 0 and N / 2 are dropped
-    const int total = t.nkb * 16 * S::XP;
+    // conj(Z), Z = A + i B, on the whole line: modes k < nxh from the rows, the
+    // rest by Hermitian symmetry; the imaginary parts of modes 0 and N / 2 are
+    // dropped
+    const int total = t.nkb * C * S::XP;
     for (int f1 = tid; f1 < total; f1 += EH * S::XTHREADS) {
-        cx<float> ra[EH], rb[EH];
+        cx<T> ra[EH], rb[EH];
 #pragma unroll
         for (int i = 0; i < EH; ++i) {
-            ra[i] = rb[i] = make_float2(0.f, 0.f);
+            ra[i] = rb[i] = cmk<T>(T(0), T(0));
             const int f = f1 + i * S::XTHREADS;
-            const int kk = f & 15, cc = (f >> 4) & (S::XP - 1), kb = f / (16 * S::XP);
-            const int k = kb * 16 + kk;
+            const int kk = f & (C - 1), cc = (f / C) & (S::XP - 1), kb = f / (C * S::XP);
+            const int k = kb * C + kk;
             const long long ga = t.g0 + 2 * cc;
             if (f < total && k < t.nxh && ga < t.lines) {
                 const long long o = kb * t.kbstride + kk;
-                ra[i] = mr_ld(in + rowoff[2 * cc] + o);
-                if (ga + 1 < t.lines) rb[i] = mr_ld(in + rowoff[2 * cc + 1] + o);
+                ra[i] = mr_ld<T>(t.in_c + rowoff[2 * cc] + o);
+                if (ga + 1 < t.lines) rb[i] = mr_ld<T>(t.in_c + rowoff[2 * cc + 1] + o);
             }
         }
 #pragma unroll
         for (int i = 0; i < EH; ++i) {
             const int f = f1 + i * S::XTHREADS;
-            const int kk = f & 15, cc = (f >> 4) & (S::XP - 1), kb = f / (16 * S::XP);
-            const int k = kb * 16 + kk;
+            const int kk = f & (C - 1), cc = (f / C) & (S::XP - 1), kb = f / (C * S::XP);
+            const int k = kb * C + kk;
             if (f < total && k < t.nxh) {
-                const cx<float> A = ra[i], B = rb[i];
-                cx<float> *col = lds + cc * S::SP;
+                const cx<T> A = ra[i], B = rb[i];
+                cx<T> *col = lds + cc * S::SP;
                 if (k == 0 || 2 * k == N) {
-                    col[k] = make_float2(A.x, B.x);
+                    col[k] = cmk<T>(A.x, -B.x);
                 } else {
-                    col[k] = make_float2(A.x - B.y, A.y + B.x);
-                    col[N - k] = make_float2(A.x + B.y, B.x - A.y);
+                    col[k] = cmk<T>(A.x - B.y, -A.y - B.x);
+                    col[N - k] = cmk<T>(A.x + B.y, A.y - B.x);
                 }
             }
         }
     }
     __syncthreads();
     const int c = tid / N2, q = tid - c * N2;
-    cx<float> x[N1];
+    cx<T> x[N1];
     if (tid < S::XP * N2) {  // step 1, item (c, q)
 #pragma unroll
         for (int m = 0; m < N1; ++m) x[m] = lds[c * S::SP + q + N2 * m];
-        DftMR<N1, 1>::run(x);
+        DftMR<T, N1>::run(x);
 #pragma unroll
-        for (int k1 = 1; k1 < N1; ++k1) {
-            cx<float> w = t.tw[q * k1];
-            w.y = -w.y;
-            x[k1] = cmul(x[k1], w);
-        }
+        for (int k1 = 1; k1 < N1; ++k1) x[k1] = cmul(x[k1], mr_ld<T>(t.tw + q * k1));
     }
     __syncthreads();  // the lines are read before the exchange tile overwrites them
     if (tid < S::XP * N2) {
@@ -514,22 +607,22 @@ __device__ __forceinline__ void mr_c2r_body(const MrX &t) {
         for (int k1 = 0; k1 < N1; ++k1) lds[(c * N1 + k1) * S::P2 + q] = x[k1];
     }
     __syncthreads();
-    if (tid < S::XP * N1) {  // step 2, item (c, k1): real parts to line 2c, imaginary to 2c + 1
+    if (tid < S::XP * N1) {  // step 2, item (c, k1): real parts to line 2c, minus imaginary to 2c + 1
         const int c2 = tid / N1, k1 = tid - c2 * N1;
-        cx<float> y[N2];
+        cx<T> y[N2];
 #pragma unroll
         for (int n2 = 0; n2 < N2; ++n2) y[n2] = lds[(c2 * N1 + k1) * S::P2 + n2];
-        DftMR<N2, 1>::run(y);
+        DftMR<T, N2>::run(y);
         const long long ga = t.g0 + 2 * c2;
         if (ga < t.lines) {
-            float *pa = out + ga * t.ld_real + k1;
+            T *pa = t.out_r + ga * t.ld_real + k1;
 #pragma unroll
-            for (int k2 = 0; k2 < N2; ++k2) mr_st(pa + N1 * k2, y[k2].x);
+            for (int k2 = 0; k2 < N2; ++k2) mr_st1(pa + N1 * k2, y[k2].x);
         }
         if (ga + 1 < t.lines) {
-            float *pb = out + (ga + 1) * t.ld_real + k1;
+            T *pb = t.out_r + (ga + 1) * t.ld_real + k1;
 #pragma unroll
-            for (int k2 = 0; k2 < N2; ++k2) mr_st(pb + N1 * k2, y[k2].y);
+            for (int k2 = 0; k2 < N2; ++k2) mr_st1(pb + N1 * k2, -y[k2].y);
         }
     }
 }
@@ -540,6 +633,7 @@ __device__ __forceinline__ void mr_c2r_body(const MrX &t) {
 struct MrArgs {
     PassArgs one;
     BatchArgs b;
+    int dir;  // C2C: -1 forward, +1 backward
 };
 
 __device__ __forceinline__ int mr_find(const BatchArgs &b, long long blk) {
@@ -552,77 +646,93 @@ __device__ __forceinline__ int mr_find(const BatchArgs &b, long long blk) {
     return lo;
 }
 
-template <int N1, int N2, int DIR>
-__global__ __launch_bounds__(mr_c2c_threads(N1, N2)) void k_mr_c2c(MrArgs m) {
+template <int N1, int N2, typename T>
+__global__ __launch_bounds__(mr_c2c_threads<T>(N1, N2)) void k_mr_c2c(MrArgs m) {
     const long long blk = blockIdx.x;
-    MrC2C t;
+    MrC2C<T> t;
     if (m.b.count == 0) {
-        t = mr_c2c_args(m.one, m.one.in, m.one.out, blk);
+        t = mr_c2c_args<T>(m.one, m.dir, m.one.in, m.one.out, blk);
     } else {
         const int i = mr_find(m.b, blk);
         const PassArgs &a = m.b.args[i];
-        t = mr_c2c_args(a, m.b.in_user ? (const void *)(m.b.user_in + (size_t)a.in) : a.in,
-                        m.b.out_user ? (void *)(m.b.user_out + (size_t)a.out) : a.out, blk - m.b.first[i]);
+        t = mr_c2c_args<T>(a, m.dir, m.b.in_user ? (const void *)(m.b.user_in + (size_t)a.in) : a.in,
+                           m.b.out_user ? (void *)(m.b.user_out + (size_t)a.out) : a.out, blk - m.b.first[i]);
     }
-    mr_c2c_body<N1, N2, DIR>(t);
+    mr_c2c_body<T, N1, N2>(t);
 }
 
-template <int N1, int N2, int FWD>
-__global__ __launch_bounds__(mr_x_threads(N1, N2)) void k_mr_x(MrArgs m) {
+template <int N1, int N2, int FWD, typename T>
+__global__ __launch_bounds__(mr_x_threads<T>(N1, N2)) void k_mr_x(MrArgs m) {
     const long long blk = blockIdx.x;
-    MrX t;
+    constexpr int XP = MrShape<T, N1, N2>::XP;
+    MrX<T> t;
     if (m.b.count == 0) {
-        t = mr_x_args(m.one, m.one.in, m.one.out, blk);
+        t = mr_x_args<T>(m.one, m.one.in, m.one.out, blk, XP);
     } else {
         const int i = mr_find(m.b, blk);
         const PassArgs &a = m.b.args[i];
-        t = mr_x_args(a, m.b.in_user ? (const void *)(m.b.user_in + (size_t)a.in) : a.in,
-                      m.b.out_user ? (void *)(m.b.user_out + (size_t)a.out) : a.out, blk - m.b.first[i]);
+        t = mr_x_args<T>(a, m.b.in_user ? (const void *)(m.b.user_in + (size_t)a.in) : a.in,
+                         m.b.out_user ? (void *)(m.b.user_out + (size_t)a.out) : a.out, blk - m.b.first[i], XP);
     }
-    if constexpr (FWD) mr_r2c_body<N1, N2>(t);
-    else mr_c2r_body<N1, N2>(t);
+    if constexpr (FWD) mr_r2c_body<T, N1, N2>(t);
+    else mr_c2r_body<T, N1, N2>(t);
 }
 
-// Lengths with a compile-time plan: X(N, N1, N2), N1 <= N2 the factor pair
-// closest to sqrt(N).  Every 7-smooth length from 48 to 320 but 256 (a
-// power-of-two kernel's), and 360, 480.  Four lists, one per compilation
-// unit (kernels_mr_p0.hip .. p3), dealt round-robin so the units take about
-// the same time to build.
-#define PF_MR_LENGTHS_0(X) \
-    X(48, 6, 8) X(56, 7, 8) X(70, 7, 10) X(81, 9, 9) X(98, 7, 14) X(112, 8, 14) X(128, 8, 16) \
-    X(147, 7, 21) X(168, 12, 14) X(192, 12, 16) X(216, 12, 18) X(243, 9, 27) X(270, 15, 18) \
-    X(300, 15, 20) X(480, 20, 24)
-#define PF_MR_LENGTHS_1(X) \
-    X(49, 7, 7) X(60, 6, 10) X(72, 8, 9) X(84, 7, 12) X(100, 10, 10) X(120, 10, 12) X(135, 9, 15) \
-    X(150, 10, 15) X(175, 7, 25) X(196, 14, 14) X(224, 14, 16) X(245, 7, 35) X(280, 14, 20) \
-    X(315, 15, 21)
-#define PF_MR_LENGTHS_2(X) \
-    X(50, 5, 10) X(63, 7, 9) X(75, 5, 15) X(90, 9, 10) X(105, 7, 15) X(125, 5, 25) X(140, 10, 14) \
-    X(160, 10, 16) X(180, 12, 15) X(200, 10, 20) X(225, 15, 15) X(250, 10, 25) X(288, 16, 18) \
-    X(320, 16, 20)
-#define PF_MR_LENGTHS_3(X) \
-    X(54, 6, 9) X(64, 8, 8) X(80, 8, 10) X(96, 8, 12) X(108, 9, 12) X(126, 9, 14) X(144, 12, 12) \
-    X(162, 9, 18) X(189, 9, 21) X(210, 14, 15) X(240, 15, 16) X(252, 14, 18) X(294, 14, 21) \
-    X(360, 18, 20)
-#define PF_MR_LENGTHS(X) PF_MR_LENGTHS_0(X) PF_MR_LENGTHS_1(X) PF_MR_LENGTHS_2(X) PF_MR_LENGTHS_3(X)
+// Lengths with a compile-time plan and their factors N1 <= N2, the pair
+// closest to sqrt(N): every 7-smooth length from 16 to 1024 whose larger
+// factor is at most 42 (all but 343 = 7 x 49 and 686 = 14 x 49, whose 49-point
+// step would not fit the registers in FP64).
+struct MrLen {
+    short n, n1, n2;
+};
+constexpr MrLen kMrLen[] = {
+    {16, 4, 4}, {18, 3, 6}, {20, 4, 5}, {21, 3, 7}, {24, 4, 6}, {25, 5, 5}, {27, 3, 9}, {28, 4, 7},
+    {30, 5, 6}, {32, 4, 8}, {35, 5, 7}, {36, 6, 6}, {40, 5, 8}, {42, 6, 7}, {45, 5, 9}, {48, 6, 8},
+    {49, 7, 7}, {50, 5, 10}, {54, 6, 9}, {56, 7, 8}, {60, 6, 10}, {63, 7, 9}, {64, 8, 8}, {70, 7, 10},
+    {72, 8, 9}, {75, 5, 15}, {80, 8, 10}, {81, 9, 9}, {84, 7, 12}, {90, 9, 10}, {96, 8, 12}, {98, 7, 14},
+    {100, 10, 10}, {105, 7, 15}, {108, 9, 12}, {112, 8, 14}, {120, 10, 12}, {125, 5, 25}, {126, 9, 14},
+    {128, 8, 16}, {135, 9, 15}, {140, 10, 14}, {144, 12, 12}, {147, 7, 21}, {150, 10, 15}, {160, 10, 16},
+    {162, 9, 18}, {168, 12, 14}, {175, 7, 25}, {180, 12, 15}, {189, 9, 21}, {192, 12, 16}, {196, 14, 14},
+    {200, 10, 20}, {210, 14, 15}, {216, 12, 18}, {224, 14, 16}, {225, 15, 15}, {240, 15, 16}, {243, 9, 27},
+    {245, 7, 35}, {250, 10, 25}, {252, 14, 18}, {256, 16, 16}, {270, 15, 18}, {280, 14, 20}, {288, 16, 18},
+    {294, 14, 21}, {300, 15, 20}, {315, 15, 21}, {320, 16, 20}, {324, 18, 18}, {336, 16, 21}, {350, 14, 25},
+    {360, 18, 20}, {375, 15, 25}, {378, 18, 21}, {384, 16, 24}, {392, 14, 28}, {400, 20, 20}, {405, 15, 27},
+    {420, 20, 21}, {432, 18, 24}, {441, 21, 21}, {448, 16, 28}, {450, 18, 25}, {480, 20, 24}, {486, 18, 27},
+    {490, 14, 35}, {500, 20, 25}, {504, 21, 24}, {512, 16, 32}, {525, 21, 25}, {540, 20, 27}, {560, 20, 28},
+    {567, 21, 27}, {576, 24, 24}, {588, 21, 28}, {600, 24, 25}, {625, 25, 25}, {630, 21, 30}, {640, 20, 32},
+    {648, 24, 27}, {672, 24, 28}, {675, 25, 27}, {700, 25, 28}, {720, 24, 30}, {729, 27, 27}, {735, 21, 35},
+    {750, 25, 30}, {756, 27, 28}, {768, 24, 32}, {784, 28, 28}, {800, 25, 32}, {810, 27, 30}, {840, 28, 30},
+    {864, 27, 32}, {875, 25, 35}, {882, 21, 42}, {896, 28, 32}, {900, 30, 30}, {945, 27, 35}, {960, 30, 32},
+    {972, 27, 36}, {980, 28, 35}, {1000, 25, 40}, {1008, 28, 36}, {1024, 32, 32},
+};
+constexpr int kMrCount = (int)(sizeof(kMrLen) / sizeof(kMrLen[0]));
 
-// kernel of the length-N1 N2 passes: what = 0 forward C2C, 1 backward C2C,
-// 2 forward X (real to half spectra), 3 backward X
-template <int N1, int N2>
-const void *mr_kernel_of(int what) {
-    static_assert(MrShape<N1, N2>::XLDS * 8 + 2 * PF_MR_XP * 8 <= 65536 && MrShape<N1, N2>::CLDS * 8 <= 65536,
-                  "tile within the default dynamic LDS limit");
+// index of length n in the table, -1 if it has no compile-time plan
+constexpr int mr_index(int n) {
+    for (int i = 0; i < kMrCount; ++i)
+        if (kMrLen[i].n == n) return i;
+    return -1;
+}
+
+// The table's instantiations are dealt round-robin over PF_MR_UNITS
+// compilation units per precision (kernels_mr_unit.hip, built once per unit).
+#ifndef PF_MR_UNITS
+#define PF_MR_UNITS 8
+#endif
+enum { MR_C2C = 0, MR_R2C = 1, MR_C2R = 2 };  // C2C columns, forward X (real to half spectra), backward X
+
+typedef const void *(*mr_pick_fn)(int index, int what);
+
+template <typename T, int I>
+const void *mr_kernel_at(int what) {
+    constexpr int N1 = kMrLen[I].n1, N2 = kMrLen[I].n2;
+    static_assert(MrShape<T, N1, N2>::XLDS <= kMaxLds && MrShape<T, N1, N2>::CLDS <= kMaxLds, "tile too large");
     switch (what) {
-        case 0: return reinterpret_cast<const void *>(&k_mr_c2c<N1, N2, -1>);
-        case 1: return reinterpret_cast<const void *>(&k_mr_c2c<N1, N2, 1>);
-        case 2: return reinterpret_cast<const void *>(&k_mr_x<N1, N2, 1>);
-        case 3: return reinterpret_cast<const void *>(&k_mr_x<N1, N2, 0>);
+        case MR_C2C: return reinterpret_cast<const void *>(&k_mr_c2c<N1, N2, T>);
+        case MR_R2C: return reinterpret_cast<const void *>(&k_mr_x<N1, N2, 1, T>);
+        case MR_C2R: return reinterpret_cast<const void *>(&k_mr_x<N1, N2, 0, T>);
     }
     return nullptr;
 }
-const void *mr_kernel_p0(int n, int what);
-const void *mr_kernel_p1(int n, int what);
-const void *mr_kernel_p2(int n, int what);
-const void *mr_kernel_p3(int n, int what);
 
 }  // namespace pf

@@ -6,35 +6,53 @@
 
 namespace pf {
 
+// the compilation units (kernels_mr_unit.hip), PF_MR_UNITS per precision
+#define PF_MR_EACH_UNIT(X, T) X(T, 0) X(T, 1) X(T, 2) X(T, 3) X(T, 4) X(T, 5) X(T, 6) X(T, 7)
+static_assert(PF_MR_UNITS == 8, "PF_MR_EACH_UNIT names every unit");
+#define PF_MR_DECLARE(T, U) const void *mr_pick_##T##_##U(int index, int what);
+PF_MR_EACH_UNIT(PF_MR_DECLARE, float)
+PF_MR_EACH_UNIT(PF_MR_DECLARE, double)
+#undef PF_MR_DECLARE
+
 namespace {
 
-bool mr_factors(int n, int *n1, int *n2) {
-#define PF_MR_CASE(N, N1, N2) \
-    case N:                   \
-        *n1 = N1;             \
-        *n2 = N2;             \
-        return true;
-    switch (n) {
-        PF_MR_LENGTHS(PF_MR_CASE)
-        default:
-            return false;
-    }
-#undef PF_MR_CASE
+struct MrSizes {  // launch shape of one length in one precision
+    int c2c_threads, x_threads, x_pairs;
+    size_t c2c_lds, x_lds;
+};
+
+template <typename T, int I>
+constexpr MrSizes sizes_at() {  // the kernels' own tile constants, so that host and device sizes agree
+    using S = MrShape<T, kMrLen[I].n1, kMrLen[I].n2>;
+    return MrSizes{S::CTHREADS, S::XTHREADS, S::XP, (size_t)S::CLDS, (size_t)S::XLDS};
+}
+template <typename T, int... I>
+const MrSizes &sizes_of(int index, std::integer_sequence<int, I...>) {
+    static constexpr MrSizes all[] = {sizes_at<T, I>()...};
+    return all[index];
+}
+const MrSizes &sizes(int index, int prec) {
+    constexpr auto seq = std::make_integer_sequence<int, kMrCount>();
+    return prec ? sizes_of<double>(index, seq) : sizes_of<float>(index, seq);
 }
 
-const void *mr_kernel(int n, int what) {
-    for (auto pick : {mr_kernel_p0, mr_kernel_p1, mr_kernel_p2, mr_kernel_p3})
-        if (const void *k = pick(n, what)) return k;
-    return nullptr;
+const void *mr_kernel(int n, int prec, int what) {
+    const int i = mr_index(n);
+    if (i < 0) return nullptr;
+#define PF_MR_REF(T, U) mr_pick_##T##_##U,
+    static const mr_pick_fn f32[] = {PF_MR_EACH_UNIT(PF_MR_REF, float)};
+    static const mr_pick_fn f64[] = {PF_MR_EACH_UNIT(PF_MR_REF, double)};
+#undef PF_MR_REF
+    return (prec ? f64 : f32)[i % PF_MR_UNITS](i, what);
 }
 
-// kernel of pass kind `kind`, direction dir (-1 forward, +1 backward)
-const void *mr_kernel_for(int kind, int dir, int n) {
-    const int what = kind == PASS_C2C_MR ? (dir < 0 ? 0 : 1) : kind == PASS_R2C_MR ? 2 : kind == PASS_C2R_MR ? 3 : -1;
-    return what < 0 ? nullptr : mr_kernel(n, what);
+int what_of(int kind) {
+    return kind == PASS_C2C_MR ? MR_C2C : kind == PASS_R2C_MR ? MR_R2C : kind == PASS_C2R_MR ? MR_C2R : -1;
 }
 
-hipError_t mr_go(const void *k, unsigned blocks, unsigned threads, size_t lds, MrArgs &m, hipStream_t s) {
+hipError_t mr_go(int kind, int n, int prec, unsigned blocks, unsigned threads, size_t lds, MrArgs &m, hipStream_t s) {
+    const int what = what_of(kind);
+    const void *k = what < 0 ? nullptr : mr_kernel(n, prec, what);
     if (!k) return hipErrorInvalidValue;
     if (blocks == 0) return hipSuccess;
     void *args[] = {&m};
@@ -43,45 +61,50 @@ hipError_t mr_go(const void *k, unsigned blocks, unsigned threads, size_t lds, M
 
 }  // namespace
 
-bool mr_supported(int n, int prec) {
-    int a, b;
-    return prec == 0 && mr_factors(n, &a, &b);
+bool mr_supported(int n, int prec) { return (prec == 0 || prec == 1) && mr_index(n) >= 0; }
+
+int mr_threads_of(int n, int prec, int xpass) {
+    const int i = mr_index(n);
+    return i < 0 ? 0 : xpass ? sizes(i, prec).x_threads : sizes(i, prec).c2c_threads;
 }
 
-int mr_threads_of(int n, int xpass) {
-    int a = 0, b = 0;
-    if (!mr_factors(n, &a, &b)) return 0;
-    return xpass ? mr_x_threads(a, b) : mr_c2c_threads(a, b);
+int mr_x_pairs(int n, int prec) {
+    const int i = mr_index(n);
+    return i < 0 ? 0 : sizes(i, prec).x_pairs;
 }
 
-int mr_x_pairs() { return PF_MR_XP; }
+size_t mr_lds_bytes(int n, int prec, int xpass) {
+    const int i = mr_index(n);
+    return i < 0 ? 0 : xpass ? sizes(i, prec).x_lds : sizes(i, prec).c2c_lds;
+}
 
-size_t mr_lds_bytes(int n, int xpass) {
-    // the kernels' own tile constants, so that host and device sizes agree
-#define PF_MR_CASE(N, N1, N2) \
-    case N:                   \
-        return (size_t)(xpass ? MrShape<N1, N2>::XLDS : MrShape<N1, N2>::CLDS) * sizeof(float2);
-    switch (n) {
-        PF_MR_LENGTHS(PF_MR_CASE)
-        default:
-            return 0;
+hipError_t mr_prepare(int n, int prec, int xpass) {
+    const size_t lds = mr_lds_bytes(n, prec, xpass);
+    if (lds <= 64 * 1024) return hipSuccess;  // the default limit
+    hipError_t e = hipSuccess;
+    for (int what : {MR_C2C, MR_R2C, MR_C2R}) {
+        if ((what != MR_C2C) != (xpass != 0) || e != hipSuccess) continue;
+        const void *k = mr_kernel(n, prec, what);
+        e = k ? hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) : hipErrorInvalidValue;
     }
-#undef PF_MR_CASE
+    return e;
 }
 
 hipError_t mr_launch(const PassDesc &d, hipStream_t s) {
     MrArgs m;
     std::memset(&m, 0, sizeof(m));
     m.one = d.a;
-    return mr_go(mr_kernel_for(d.kind, d.dir, d.a.fft.n), d.blocks, d.threads, d.lds, m, s);
+    m.dir = d.dir;
+    return mr_go(d.kind, d.a.fft.n, d.prec, d.blocks, d.threads, d.lds, m, s);
 }
 
 hipError_t mr_launch_batch(const BatchLaunch &L, hipStream_t s) {
     MrArgs m;
     std::memset(&m, 0, sizeof(m));
     m.b = L.b;
+    m.dir = L.dir;
     if (m.b.count < 1) return hipErrorInvalidValue;
-    return mr_go(mr_kernel_for(L.kind, L.dir, L.n), L.blocks, L.threads, L.lds, m, s);
+    return mr_go(L.kind, L.n, L.prec, L.blocks, L.threads, L.lds, m, s);
 }
 
 }  // namespace pf

@@ -45,7 +45,7 @@ enum PassKind {
     PASS_FILL = 7,
     PASS_BOX = 8,
     PASS_FUSED_XY = 9,  // launched by the planner from its FusedArgs (p2_fused_launch)
-    PASS_C2C_MR = 10,   // compile-time mixed-radix passes (kernels_mr.h), FP32
+    PASS_C2C_MR = 10,   // compile-time mixed-radix passes (kernels_mr.h)
     PASS_R2C_MR = 11,
     PASS_C2R_MR = 12
 };
@@ -210,14 +210,16 @@ const void *p2_fused_symbol(int nx, int ny, int fwd);
 hipError_t p2_xcd_queues(unsigned blocks, int *nq);
 hipError_t p2_fused_launch(const FusedArgs &f, int fwd, int nx, int ny, unsigned blocks, hipStream_t s);
 
-// Compile-time mixed-radix passes, FP32 (kernels_mr.hip): the C2C column pass
-// (PASS_C2C_MR, 16 columns per tile, a.tc_log2 = 4) and the X passes
-// (PASS_R2C_MR / PASS_C2R_MR, mr_x_pairs() line pairs per tile) of a length n the table
-// holds; one tile per workgroup.  a.tw: W_n^m, m < n (forward sign).
+// Compile-time mixed-radix passes (kernels_mr.hip), FP32 and FP64: the C2C
+// column pass (PASS_C2C_MR, one 128-byte row of columns per tile) and the X
+// passes (PASS_R2C_MR / PASS_C2R_MR, mr_x_pairs() line pairs per tile) of a
+// length n the table holds; one tile per workgroup.  a.tw: W_n^m, m < n
+// (forward sign).
 bool mr_supported(int n, int prec);
-int mr_threads_of(int n, int xpass);  // threads per workgroup of the C2C (xpass 0) or X kernel
-int mr_x_pairs();                     // line pairs per X tile (a power of two)
-size_t mr_lds_bytes(int n, int xpass);
+int mr_threads_of(int n, int prec, int xpass);  // threads per workgroup of the C2C (xpass 0) or X kernel
+int mr_x_pairs(int n, int prec);                // line pairs per X tile (a power of two)
+size_t mr_lds_bytes(int n, int prec, int xpass);
+hipError_t mr_prepare(int n, int prec, int xpass);  // allow the kernels their dynamic LDS
 hipError_t mr_launch(const PassDesc &d, hipStream_t s);
 hipError_t mr_launch_batch(const BatchLaunch &L, hipStream_t s);
 
