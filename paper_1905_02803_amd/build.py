@@ -18,6 +18,10 @@ MR_UNITS = 8
 MR_PARTS = {f"kernels_mr_{t}_{u}.hip": [f"-DPF_MR_UNIT={u}", f"-DPF_MR_UNITS={MR_UNITS}", f"-DPF_MR_T={t}",
                                         f"-DPF_MR_NAME=mr_pick_{t}_{u}"]
             for t in ("double", "float") for u in range(MR_UNITS)}
+MR_CLASSES = 3  # classes of lengths with a batched kernel (kernels_mr.h, kMrClass)
+MR_PARTS.update({f"kernels_mr_class_{t}_{c}.hip": [f"-DPF_MR_CLASS={c}", f"-DPF_MR_T={t}",
+                                                   f"-DPF_MR_NAME=mr_class_{t}_{c}"]
+                 for t in ("double", "float") for c in range(MR_CLASSES)})
 # object names (with .hip in place of .o), the slowest to compile first
 SOURCES = ["kernels_p2.hip", *MR_PARTS, "capi.hip", "kernels.hip", "kernels_mr.hip"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
@@ -39,7 +43,8 @@ def build(verbose: bool = False, out: str = LIB, extra=()) -> str:
     cmds = []
     for src in SOURCES:
         obj = os.path.join(bdir, src.replace(".hip", ".o"))
-        path = os.path.join(CSRC, "kernels_mr_unit.hip" if src in MR_PARTS else src)
+        path = os.path.join(CSRC, src if src not in MR_PARTS else
+                            "kernels_mr_class.hip" if "_class_" in src else "kernels_mr_unit.hip")
         cmds.append([HIPCC] + FLAGS + list(extra) + MR_PARTS.get(src, []) + inc + ["-c", path, "-o", obj])
         if verbose:
             print(" ".join(cmds[-1]), flush=True)

@@ -331,11 +331,6 @@ void set_c2c_common(PassDesc &d, const pf_plan *p, const FftSpec &fs, size_t two
 #ifndef PF_TILE_ORDER_Y
 #define PF_TILE_ORDER_Y 0
 #endif
-// mixed-radix Z passes: order 1 (ky fastest) measured within 1% of order 0 at
-// 480 x 360 x 250, 320^3 and on the 64-transform batch
-#ifndef PF_TILE_ORDER_MRZ
-#define PF_TILE_ORDER_MRZ 0
-#endif
 #ifndef PF_XCD_UROWS
 #define PF_XCD_UROWS 1
 #endif
@@ -712,7 +707,6 @@ void build_passes(pf_plan *p) {
         // walking column blocks first, so that neighbouring tiles (on one XCD)
         // share the cache lines the rows straddle
         z.a.tile_order = dir == 0 ? PF_TILE_ORDER_FZ : (p->lay.stride1 ? PF_TILE_ORDER_BZ : 0);
-        if (z.kind == pf::PASS_C2C_MR) z.a.tile_order = PF_TILE_ORDER_MRZ;
         z.blocks = c2c_grid(p, z);
 
         if ((dir == 1 && p->bwd_tr) || (dir == 0 && p->fwd_tr)) {
@@ -1021,6 +1015,18 @@ int pf_query_dims(int nx, int ny, int nz, const pf_layout *l, int pencil, int r1
     return PF_OK;
 }
 
+// The mixed-radix kernels address one tile by 32-bit byte offsets from its base:
+// whether every tile of axis i stays below 4 GB.  X: the lines of a tile lie in
+// at most 31 / ny + 2 planes of the workspace; Z: a step reaches over N2 planes (of
+// the workspace or of [nz][ny][nxh], which is no larger), or over 16 lines ny nz
+// apart; Y tiles lie in one plane, and need only that to be below 4 GB.
+static bool mr_fits(const pf_plan *p, int i) {
+    const unsigned long long lim = 1ULL << 32, plane = (unsigned long long)p->zrows * 128;
+    if (i == 0) return (31 / p->ny + 2) * plane < lim;
+    if (i == 1) return plane < lim;
+    return pf::mr_long_factor(p->nz) * plane < lim && 16ULL * p->ny * p->nz * p->csize < lim;
+}
+
 static int plan_create(int nx, int ny, int nz, const pf_layout *l, const PlanOpts &o, pf_plan **out) {
     if (!out) return PF_EINVAL;
     *out = nullptr;
@@ -1101,7 +1107,7 @@ static int plan_create(int nx, int ny, int nz, const pf_layout *l, const PlanOpt
     const int axis_n[3] = {nx, ny, nz};
     for (int i = 0; i < 3; ++i) {
         p->mr[i] = !o.no_mr && pf::mr_supported(axis_n[i], l->precision) && !(i == 0 && p->fast_x) &&
-                   !(i == 2 && l->third != PF_THIRD_FFT);
+                   !(i == 2 && l->third != PF_THIRD_FFT) && mr_fits(p, i);
         p->tw_mr[i] = 0;
         if (!p->mr[i]) continue;
         p->tw_mr[i] = host.size();
@@ -1693,7 +1699,8 @@ int pf_batch_setup(int count, const int *dims, const pf_layout *l, const pf_tune
             const bool xpass = (dir == 0 && k == 0) || (dir == 1 && k == 2);
             const int in_user = k == 0, out_user = k == 2;
             // launch groups: runtime-radix passes by block size; compile-time
-            // mixed-radix passes by length (one kernel per length)
+            // mixed-radix passes by class of lengths (one kernel per class), or by
+            // length where there is none
             auto is_mr = [](pf::PassKind kd) {
                 return kd == pf::PASS_C2C_MR || kd == pf::PASS_R2C_MR || kd == pf::PASS_C2R_MR;
             };
@@ -1701,9 +1708,15 @@ int pf_batch_setup(int count, const int *dims, const pf_layout *l, const pf_tune
                 const PassDesc &d = b->plans[i]->pass[dir][k];
                 return is_mr(d.kind) ? d.a.fft.n : 0;
             };
+            auto mr_cls = [&](int i) {
+                const int n = mr_len(i);
+                return n ? pf::mr_batch_class(n) : -1;
+            };
             auto same_group = [&](int u, int v) {
                 const PassDesc &du = b->plans[u]->pass[dir][k], &dv = b->plans[v]->pass[dir][k];
-                return du.kind == dv.kind && mr_len(u) == mr_len(v) && du.threads == dv.threads;
+                if (du.kind != dv.kind) return false;
+                if (mr_cls(u) >= 0 || mr_cls(v) >= 0) return mr_cls(u) == mr_cls(v);
+                return mr_len(u) == mr_len(v) && du.threads == dv.threads;
             };
             for (int i = 0; i < count; ++i) {
                 order[i] = i;
@@ -1730,6 +1743,7 @@ int pf_batch_setup(int count, const int *dims, const pf_layout *l, const pf_tune
                 L.dir = d0.dir;
                 L.prec = d0.prec;
                 L.n = mr_len(lead);
+                L.cls = mr_cls(lead);
                 L.threads = thr;
                 L.b.in_user = in_user;
                 L.b.out_user = out_user;
@@ -1745,6 +1759,10 @@ int pf_batch_setup(int count, const int *dims, const pf_layout *l, const pf_tune
                     const size_t uoff = xpass ? b->roff[i] : b->coff[i];
                     A[j].in = in_user ? (const void *)uoff : (const void *)w;
                     A[j].out = out_user ? (void *)uoff : (void *)w;
+                    if (is_mr(d.kind)) {  // packed records from the group's first slot on (smaller than the slots)
+                        const PassArgs full = A[j];
+                        pf::mr_entry(d.kind, d.dir, d.prec, full, (char *)(A + (j - n)) + n * pf::mr_entry_bytes());
+                    }
                     F[f + n] = blocks;
                     blocks += d.blocks;
                     L.lds = std::max(L.lds, d.lds);

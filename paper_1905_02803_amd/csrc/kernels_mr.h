@@ -18,10 +18,10 @@
 //
 // Bound by the HBM traffic of the pass; measured against the runtime-radix
 // kernels, which staged the tile in LDS and read their twiddles per radix stage
-// (ms per R2C + C2R pair): FP64 300 x 280 x 250 0.675 -> 0.415 (Y pass 2.55 ->
-// 5.87 TB/s), FP64 600 x 400 x 450 3.95 -> 2.28, FP32 768 x 768 x 384 3.27 ->
-// 2.49, FP32 384^3 in natural order 0.897 -> 0.668, FP32 36 x 20 x 24 0.049 ->
-// 0.028 (8.2 against 4.7 us per pass).
+// (ms per R2C + C2R pair): FP64 300 x 280 x 250 0.675 -> 0.392 (Y pass 2.55 ->
+// 6.0 TB/s), FP64 600 x 400 x 450 3.95 -> 2.28, FP32 768 x 768 x 384 3.27 ->
+// 2.45, FP32 384^3 in natural order 0.897 -> 0.672, FP32 36 x 20 x 24 0.049 ->
+// 0.026 (8.2 against 4.4 us per pass).
 //
 // Long lengths exchange the real and the imaginary parts one after the other
 // through half the LDS (MrShape::SPLIT), so that several workgroups still fit
@@ -37,6 +37,9 @@
 // the lines, and the real/complex split (forward) or the Hermitian fill
 // (backward) goes through LDS.
 #pragma once
+
+#include <type_traits>
+#include <utility>
 
 #include "fft_device.h"
 #include "pf_internal.h"
@@ -196,6 +199,7 @@ __host__ __device__ constexpr int mr_xp(int n1, int n2) {
     const int xp = n2 >= 16 ? 4 : n2 >= 8 ? 8 : 16;
     return xp == 4 && 4 * n1 * n2 * (int)sizeof(cx<T>) > 40960 ? 2 : xp;
 }
+constexpr int kMrRows = 32;  // lines of the widest X tile
 // X kernels: pairs x max(N1, N2) items, whole waves
 template <typename T>
 __host__ __device__ constexpr int mr_x_threads(int n1, int n2) {
@@ -214,6 +218,7 @@ struct MrShape {
     // pair at pitch SP (= 16 mod 32, >= N)
     static constexpr int XP = mr_xp<T>(N1, N2);
     static constexpr int XTHREADS = mr_x_threads<T>(N1, N2);
+    static constexpr int NXH = N / 2 + 1, NKB = (NXH + C - 1) / C;  // modes and column blocks of a line
     static constexpr int SP = N + ((16 - N % 32) % 32 + 32) % 32;
     static constexpr int XLDS = (XP * N1 * P2 > XP * SP ? XP * N1 * P2 : XP * SP) * (int)sizeof(cx<T>);
     // C2C pass with a line side: line-major tile copy at pitch SPZ >= N, written
@@ -230,71 +235,102 @@ struct MrShape {
 };
 
 // ---- global accesses -------------------------------------------------------------
-// Through pointers qualified as global memory: the kernels take their pointers
-// from the plan's arguments or from a batch's table, so the compiler cannot tell
-// that they are not LDS, and unqualified ones become flat accesses, which also
-// take the LDS path and its wait counter.
+// A workgroup-uniform base pointer and a 32-bit byte offset per lane: one address
+// register per access in flight instead of two, which is what bounds how many
+// waves fit (18 x 20 in FP32: 114 registers with 64-bit addresses, 81 so).  The planner
+// keeps passes whose tiles span 4 GB or more on the runtime-radix kernels.  The bases are qualified as global memory: they come from the
+// plan's arguments or a batch's table, so the compiler cannot tell that they are
+// not LDS, and would make flat accesses, which also take the LDS path and its
+// wait counter.
 #define PF_GLOBAL __attribute__((address_space(1)))
+// v passed through an empty asm statement: what is derived from it is computed
+// again instead of being held in registers from its first use on
+__device__ __forceinline__ int mr_fresh(int v) {
+    asm volatile("" : "+v"(v));
+    return v;
+}
 template <typename T>
-__device__ __forceinline__ cx<T> mr_ld(const cx<T> *p) {
+__device__ __forceinline__ cx<T> mr_ld(const void *base, unsigned off) {
     typedef T v2 __attribute__((ext_vector_type(2)));
-    const v2 u = *(const PF_GLOBAL v2 *)p;
+    const v2 u = *(const PF_GLOBAL v2 *)((const PF_GLOBAL char *)base + off);
     return cmk<T>(u.x, u.y);
 }
 template <typename T>
-__device__ __forceinline__ T mr_ld1(const T *p) {
-    return *(const PF_GLOBAL T *)p;
+__device__ __forceinline__ T mr_ld1(const void *base, unsigned off) {
+    return *(const PF_GLOBAL T *)((const PF_GLOBAL char *)base + off);
 }
-template <typename T>
-__device__ __forceinline__ void mr_st(cx<T> *p, cx<T> v) {
+// PIN (FP64 values that travelled LDS in halves): the parts pass through an empty
+// asm statement first, so that they are not held as one 4-register value from
+// the first half's arrival on (25 x 40: 260 registers spilled)
+template <typename T, bool PIN = false>
+__device__ __forceinline__ void mr_st(void *base, unsigned off, cx<T> v) {
     typedef T v2 __attribute__((ext_vector_type(2)));
+    if constexpr (PIN && sizeof(T) == 8) asm volatile("" : "+v"(v.x), "+v"(v.y));
     const v2 u = {v.x, v.y};
-    *(PF_GLOBAL v2 *)p = u;
+    *(PF_GLOBAL v2 *)((PF_GLOBAL char *)base + off) = u;
 }
 template <typename T>
-__device__ __forceinline__ void mr_st1(T *p, T v) {
-    *(PF_GLOBAL T *)p = v;
+__device__ __forceinline__ void mr_st1(void *base, unsigned off, T v) {
+    *(PF_GLOBAL T *)((PF_GLOBAL char *)base + off) = v;
 }
 
-// ---- C2C column tile -----------------------------------------------------------
-template <typename T>
-struct MrC2C {
-    const cx<T> *in;
-    cx<T> *out;
-    const cx<T> *tw;  // W_N^m, m < N (forward sign)
-    long long ib, isc, isp, ob, osc, osp;
-    int ncol;
-    T sgn;  // +1 forward, -1 backward (the sign of the imaginary parts)
+// ---- launch arguments --------------------------------------------------------------
+// 64 bytes, the whole kernel argument segment: a launch with a larger one costs
+// the host 3.6 .. 4.0 us against 2.65 us, and passes of small grids (3 us each
+// on the device) wait for the host.  Read in one piece, they also shorten a
+// pass by 0.4 us (FP64 64^3 replayed from a graph 24.7 -> 22.2 us per pair).
+// Strides are in elements; every one of a
+// grid up to 8192^3 fits 32 bits.
+enum : unsigned { MR_BACKWARD = 1, MR_IN_LINES = 2, MR_OUT_LINES = 4, MR_BATCH = 8, MR_IN_USER = 16, MR_OUT_USER = 32 };
+struct MrArgs {
+    const void *in;
+    void *out;
+    const void *tw;  // W_n^m, m < n (forward sign)
+    union {
+        // C2C: per side (i, o) the strides of the outer index, of a column block and
+        // of a point (rows) or a column (lines)
+        struct {
+            unsigned isa, isb, iss, osa, osb, oss;
+        } c;
+        // X: rows of the workspace between z planes and column blocks, row of line
+        // y = 0, lines per plane, lines
+        struct {
+            unsigned zrows, kbrows, y0, ny, lines;
+        } x;
+        // MR_BATCH: in, out are the caller's arrays; transform i owns workgroups
+        // first[i] .. first[i + 1] - 1 and runs with table[i], whose in (MR_IN_USER)
+        // or out (MR_OUT_USER) is a byte offset into them
+        struct {
+            const MrArgs *table;
+            const long long *first;
+        } b;
+    };
+    int C, CB;       // C2C: valid columns, column blocks
+    unsigned flags;
+    int count;       // MR_BATCH: transforms
 };
+static_assert(sizeof(MrArgs) == 64, "one 64-byte argument segment");
 
-template <int C>
-__device__ __forceinline__ long long mr_side_base(const Side &s, long long a, int cb) {
-    const int cpb = (int)s.cpb;
-    const int blk = cb / cpb;
-    return a * s.sa + (long long)blk * s.sblk + (long long)((cb - blk * cpb) * C) * s.sc;
+__device__ __forceinline__ int mr_find(const long long *first, int count, long long blk) {
+    int lo = 0, hi = count - 1;
+    while (lo < hi) {
+        const int mid = (lo + hi + 1) >> 1;
+        if (first[mid] <= blk) lo = mid;
+        else hi = mid - 1;
+    }
+    return lo;
 }
 
-// tile `tile` of the C2C pass a, reading inp, writing outp
-template <typename T>
-__device__ __forceinline__ MrC2C<T> mr_c2c_args(const PassArgs &a, int dir, const void *inp, void *outp,
-                                                long long tile) {
-    constexpr int C = mr_cols<T>();
-    MrC2C<T> t;
-    // tile order 1 walks the outer index fastest (neighbouring tiles then touch
-    // adjacent rows and lines of sides whose column blocks lie far apart)
-    const int CB = (int)a.CB, A = (int)a.A;
-    const int ta = a.tile_order ? (int)tile % A : (int)tile / CB;
-    const int cb = a.tile_order ? (int)tile / A : (int)tile - ta * CB;
-    t.in = reinterpret_cast<const cx<T> *>(inp);
-    t.out = reinterpret_cast<cx<T> *>(outp);
-    t.tw = reinterpret_cast<const cx<T> *>(a.tw);
-    t.ib = mr_side_base<C>(a.in_s, ta, cb);
-    t.ob = mr_side_base<C>(a.out_s, ta, cb);
-    t.isc = a.in_s.sc, t.isp = a.in_s.sp, t.osc = a.out_s.sc, t.osp = a.out_s.sp;
-    const int left = a.C - cb * C;
-    t.ncol = left < C ? left : C;
-    t.sgn = dir < 0 ? T(1) : T(-1);
-    return t;
+// The transform of this workgroup and its tile (returned): m itself, or the
+// batch entry with its pointers resolved.
+__device__ __forceinline__ unsigned mr_resolve(const MrArgs &m, MrArgs &a) {
+    a = m;
+    if (!(m.flags & MR_BATCH)) return blockIdx.x;
+    const int i = mr_find(m.b.first, m.count, blockIdx.x);
+    a = m.b.table[i];
+    if (m.flags & MR_IN_USER) a.in = (const char *)m.in + (size_t)a.in;
+    if (m.flags & MR_OUT_USER) a.out = (char *)m.out + (size_t)a.out;
+    return (unsigned)(blockIdx.x - m.b.first[i]);
 }
 
 // ---- a trip through LDS ---------------------------------------------------------
@@ -322,26 +358,43 @@ __device__ __forceinline__ void mr_trip(PUT put, GET get) {
     }
 }
 
-template <typename T, int N1, int N2>
-__device__ __forceinline__ void mr_c2c_body(const MrC2C<T> &t) {
+template <typename T, int K, bool ON>
+__device__ __forceinline__ void mr_zero(cx<T> (&v)[K]) {
+    if constexpr (ON) {
+#pragma unroll
+        for (int i = 0; i < K; ++i) v[i] = cmk<T>(T(0), T(0));
+    }
+}
+
+// One tile of the C2C pass: column block cb of outer index ta.
+// CT threads per column (N1 <= CT), each with up to I1 step-1 items.
+template <typename T, int N1, int N2, int CT>
+__device__ __forceinline__ void mr_c2c_body(const MrArgs &a, unsigned ta, unsigned cb) {
     using S = MrShape<T, N1, N2>;
     constexpr int N = S::N, C = S::C;
-    constexpr int NT = S::CTHREADS;
+    constexpr int NT = C * CT, I1 = (N2 + CT - 1) / CT;
+    static_assert(N1 <= CT, "step 2 has one item per thread");
     constexpr int ITEMS = (C * N + NT - 1) / NT;  // tile points per thread
+    constexpr unsigned CS = sizeof(cx<T>);
     const int tid = threadIdx.x;
     const int c = tid & (C - 1), j = tid / C;
-    const bool cv = c < t.ncol;
+    const int ncol = a.C - (int)cb * C;  // valid columns of the tile (may exceed C)
+    const bool cv = c < ncol;
+    const T sgn = (a.flags & MR_BACKWARD) ? T(-1) : T(1);
+    const cx<T> *tw = reinterpret_cast<const cx<T> *>(a.tw);
+    const cx<T> *in = reinterpret_cast<const cx<T> *>(a.in) + (size_t)ta * a.c.isa + (size_t)cb * a.c.isb;
+    cx<T> *out = reinterpret_cast<cx<T> *>(a.out) + (size_t)ta * a.c.osa + (size_t)cb * a.c.osb;
     // a side whose columns are whole lines (points contiguous) goes through a
     // line-major LDS copy of the tile, so that its global accesses run along
     // the points; a row side is read / written by the step-1 / step-2 threads
-    const bool in_lines = t.isp == 1 && t.isc != 1;
-    const bool out_lines = t.osp == 1 && t.osc != 1;
-    // step 1, item q = j: the N1 points q + N2 m of column c (arrays zeroed
-    // before conditional fills: the compiler otherwise keeps FP64 ones in scratch
-    // memory)
-    cx<T> x[N1];
+    const bool in_lines = (a.flags & MR_IN_LINES) != 0;
+    const bool out_lines = (a.flags & MR_OUT_LINES) != 0;
+    // step 1, items q = j + it CT: the N1 points q + N2 m of column c (arrays zeroed
+    // before conditional fills, SPLIT aside: the compiler otherwise keeps FP64
+    // ones in scratch memory)
+    cx<T> x[I1][N1];
 #pragma unroll
-    for (int m = 0; m < N1; ++m) x[m] = cmk<T>(T(0), T(0));
+    for (int it = 0; it < I1; ++it) mr_zero<T, N1, !S::SPLIT>(x[it]);
     if (in_lines) {
         cx<T> r[ITEMS];
 #pragma unroll
@@ -349,10 +402,11 @@ __device__ __forceinline__ void mr_c2c_body(const MrC2C<T> &t) {
             const int f = tid + i * NT;
             const int cc = f / N, p = f - cc * N;
             r[i] = cmk<T>(T(0), T(0));
-            if (f < C * N && cc < t.ncol) r[i] = mr_ld<T>(t.in + t.ib + cc * t.isc + p);
+            if (f < C * N && cc < ncol) r[i] = mr_ld<T>(in, ((unsigned)cc * a.c.iss + p) * CS);
         }
         mr_trip<T, S::SPLIT>(
             [&](auto w) {
+                const int tid = mr_fresh(threadIdx.x);
 #pragma unroll
                 for (int i = 0; i < ITEMS; ++i) {
                     const int f = tid + i * NT;
@@ -361,33 +415,50 @@ __device__ __forceinline__ void mr_c2c_body(const MrC2C<T> &t) {
                 }
             },
             [&](auto g) {
-                if (j < N2) {
 #pragma unroll
-                    for (int m = 0; m < N1; ++m) g(c * S::SPZ + j + N2 * m, x[m]);
+                for (int it = 0; it < I1; ++it) {
+                    const int q = j + it * CT;
+                    if (q < N2) {
+#pragma unroll
+                        for (int m = 0; m < N1; ++m) g(c * S::SPZ + q + N2 * m, x[it][m]);
+                    }
                 }
             });
-    } else if (j < N2 && cv) {
-        const cx<T> *src = t.in + t.ib + c * t.isc + j * t.isp;
-        const long long step = (long long)N2 * t.isp;
+    } else {
+        const size_t step = (size_t)N2 * a.c.iss;
 #pragma unroll
-        for (int m = 0; m < N1; ++m) x[m] = mr_ld<T>(src + m * step);
+        for (int it = 0; it < I1; ++it) {
+            const int q = j + it * CT;
+            if (q < N2 && cv) {
+                const unsigned off = ((unsigned)q * a.c.iss + c) * CS;
+#pragma unroll
+                for (int m = 0; m < N1; ++m) x[it][m] = mr_ld<T>(in + m * step, off);
+            }
+        }
     }
-    if (j < N2) {
 #pragma unroll
-        for (int m = 0; m < N1; ++m) x[m].y *= t.sgn;
-        DftMR<T, N1>::run(x);
+    for (int it = 0; it < I1; ++it) {
+        const int q = j + it * CT;
+        if (q < N2) {
 #pragma unroll
-        for (int k1 = 1; k1 < N1; ++k1) x[k1] = cmul(x[k1], mr_ld<T>(t.tw + j * k1));
+            for (int m = 0; m < N1; ++m) x[it][m].y *= sgn;
+            DftMR<T, N1>::run(x[it]);
+#pragma unroll
+            for (int k1 = 1; k1 < N1; ++k1) x[it][k1] = cmul(x[it][k1], mr_ld<T>(tw, q * k1 * CS));
+        }
     }
     if (in_lines) __syncthreads();  // the staged lines are read before the exchange tile overwrites them
     cx<T> y[N2];
-#pragma unroll
-    for (int n2 = 0; n2 < N2; ++n2) y[n2] = cmk<T>(T(0), T(0));
+    mr_zero<T, N2, !S::SPLIT>(y);
     mr_trip<T, S::SPLIT>(
         [&](auto w) {
-            if (j < N2) {
 #pragma unroll
-                for (int k1 = 0; k1 < N1; ++k1) w((k1 * S::P2 + j) * C + c, x[k1]);
+            for (int it = 0; it < I1; ++it) {
+                const int q = j + it * CT;
+                if (q < N2) {
+#pragma unroll
+                    for (int k1 = 0; k1 < N1; ++k1) w((k1 * S::P2 + q) * C + c, x[it][k1]);
+                }
             }
         },
         [&](auto g) {
@@ -398,14 +469,11 @@ __device__ __forceinline__ void mr_c2c_body(const MrC2C<T> &t) {
         });
     if (j < N1) {  // step 2, item k1 = j: outputs k1 + N1 k2 of column c
         DftMR<T, N2>::run(y);
-#pragma unroll
-        for (int k2 = 0; k2 < N2; ++k2) y[k2].y *= t.sgn;
     }
     if (out_lines) {
         __syncthreads();  // the exchange tile is read before the line-major copy overwrites it
         cx<T> r[ITEMS];
-#pragma unroll
-        for (int i = 0; i < ITEMS; ++i) r[i] = cmk<T>(T(0), T(0));
+        mr_zero<T, ITEMS, !S::SPLIT>(r);
         mr_trip<T, S::SPLIT>(
             [&](auto w) {
                 if (j < N1) {
@@ -414,6 +482,7 @@ __device__ __forceinline__ void mr_c2c_body(const MrC2C<T> &t) {
                 }
             },
             [&](auto g) {
+                const int tid = mr_fresh(threadIdx.x);
 #pragma unroll
                 for (int i = 0; i < ITEMS; ++i) {
                     const int f = tid + i * NT;
@@ -421,93 +490,64 @@ __device__ __forceinline__ void mr_c2c_body(const MrC2C<T> &t) {
                     if (f < C * N) g(cc * S::SPZ + p, r[i]);
                 }
             });
+        const int tid = mr_fresh(threadIdx.x);
 #pragma unroll
         for (int i = 0; i < ITEMS; ++i) {
             const int f = tid + i * NT;
             const int cc = f / N, p = f - cc * N;
-            if (f < C * N && cc < t.ncol) mr_st<T>(t.out + t.ob + cc * t.osc + p, r[i]);
+            if (f < C * N && cc < ncol) mr_st<T, S::SPLIT>(out, ((unsigned)cc * a.c.oss + p) * CS, cmk<T>(r[i].x, r[i].y * sgn));
         }
     } else if (j < N1 && cv) {
-        cx<T> *dst = t.out + t.ob + c * t.osc + j * t.osp;
-        const long long step = (long long)N1 * t.osp;
+        const unsigned off = ((unsigned)j * a.c.oss + c) * CS;
+        const size_t step = (size_t)N1 * a.c.oss;
 #pragma unroll
-        for (int k2 = 0; k2 < N2; ++k2) mr_st<T>(dst + k2 * step, y[k2]);
+        for (int k2 = 0; k2 < N2; ++k2) mr_st<T, S::SPLIT>(out + k2 * step, off, cmk<T>(y[k2].x, y[k2].y * sgn));
     }
 }
 
 // ---- X passes: XP pairs of real lines per tile ----------------------------------
-template <typename T>
-struct MrX {
-    const T *in_r;       // forward input
-    const cx<T> *in_c;   // backward input
-    T *out_r;            // backward output
-    cx<T> *out_c;        // forward output
-    const cx<T> *tw;     // W_N^m, m < N = nx (forward sign)
-    long long g0, lines, ld_real, ny, zrows, kbstride;
-    int y0, nkb, nxh;
-};
-
-template <typename T>
-__device__ __forceinline__ MrX<T> mr_x_args(const PassArgs &a, const void *inp, void *outp, long long tile, int xp) {
-    MrX<T> t;
-    t.in_r = reinterpret_cast<const T *>(inp);
-    t.in_c = reinterpret_cast<const cx<T> *>(inp);
-    t.out_r = reinterpret_cast<T *>(outp);
-    t.out_c = reinterpret_cast<cx<T> *>(outp);
-    t.tw = reinterpret_cast<const cx<T> *>(a.tw);
-    t.g0 = tile * (2 * xp);
-    t.lines = a.lines;
-    t.ld_real = a.ld_real;
-    t.ny = a.ny;
-    t.zrows = a.zrows;
-    t.kbstride = a.kbrows * mr_cols<T>();
-    t.y0 = a.y0;
-    t.nkb = a.nkb;
-    t.nxh = a.nxh;
-    return t;
-}
-
-// row offset (workspace, column block 0) of the 2 XP lines of the tile:
-// line g = z ny + y starts at row z zrows + y0 + y
+// Workspace rows (column block 0) of the 2 XP lines of the tile, relative to the
+// first one's (returned): line g = z ny + y is row z zrows + y0 + y.
 template <typename T, int XP>
-__device__ __forceinline__ void mr_rowoff(const MrX<T> &t, long long *rowoff) {
-    const int tid = threadIdx.x;
+__device__ __forceinline__ size_t mr_rows(const MrArgs &a, unsigned g0, unsigned *row) {
+    const unsigned tid = threadIdx.x;
+    const unsigned z0 = g0 / a.x.ny, y0 = g0 - z0 * a.x.ny;
     if (tid < 2 * XP) {
-        const long long g = t.g0 + tid;
-        const long long z = g / t.ny;
-        const long long y = g - z * t.ny;
-        rowoff[tid] = (z * t.zrows + t.y0 + y) * mr_cols<T>();
+        const unsigned g = g0 + tid, z = g / a.x.ny;
+        row[tid] = (z - z0) * a.x.zrows + (g - z * a.x.ny) - y0;
     }
+    return (size_t)z0 * a.x.zrows + a.x.y0 + y0;
 }
 
 // forward: real lines -> half spectra in the blocked workspace
-template <typename T, int N1, int N2>
-__device__ __forceinline__ void mr_r2c_body(const MrX<T> &t) {
+template <typename T, int N1, int N2, int NT>
+__device__ __forceinline__ void mr_r2c_body(const MrArgs &a, unsigned tile, unsigned *row) {
     using S = MrShape<T, N1, N2>;
     constexpr int N = S::N, C = S::C;
-    __shared__ long long rowoff[2 * S::XP];
+    constexpr unsigned CS = sizeof(cx<T>), RS = sizeof(T);
     cx<T> *lds = reinterpret_cast<cx<T> *>(pf_smem);
     const int tid = threadIdx.x;
-    mr_rowoff<T, S::XP>(t, rowoff);
+    const unsigned g0 = tile * (2 * S::XP), lines = a.x.lines;
+    const cx<T> *tw = reinterpret_cast<const cx<T> *>(a.tw);
+    const T *in = reinterpret_cast<const T *>(a.in) + (size_t)g0 * N;
+    cx<T> *out = reinterpret_cast<cx<T> *>(a.out) + mr_rows<T, S::XP>(a, g0, row) * C;
     if (tid < S::XP * N2) {  // step 1, item (c, q): lanes along the points of the lines
         const int c = tid / N2, q = tid - c * N2;
-        const long long ga = t.g0 + 2 * c;
+        const unsigned ga = g0 + 2 * c;
         cx<T> x[N1];
 #pragma unroll
         for (int m = 0; m < N1; ++m) x[m] = cmk<T>(T(0), T(0));
-        if (ga < t.lines) {
-            const T *pa = t.in_r + ga * t.ld_real + q;
+        if (ga < lines) {
 #pragma unroll
-            for (int m = 0; m < N1; ++m) x[m].x = mr_ld1(pa + N2 * m);
+            for (int m = 0; m < N1; ++m) x[m].x = mr_ld1<T>(in, (2 * c * N + q + N2 * m) * RS);
         }
-        if (ga + 1 < t.lines) {
-            const T *pb = t.in_r + (ga + 1) * t.ld_real + q;
+        if (ga + 1 < lines) {
 #pragma unroll
-            for (int m = 0; m < N1; ++m) x[m].y = mr_ld1(pb + N2 * m);
+            for (int m = 0; m < N1; ++m) x[m].y = mr_ld1<T>(in, ((2 * c + 1) * N + q + N2 * m) * RS);
         }
         DftMR<T, N1>::run(x);
 #pragma unroll
-        for (int k1 = 1; k1 < N1; ++k1) x[k1] = cmul(x[k1], mr_ld<T>(t.tw + q * k1));
+        for (int k1 = 1; k1 < N1; ++k1) x[k1] = cmul(x[k1], mr_ld<T>(tw, q * k1 * CS));
 #pragma unroll
         for (int k1 = 0; k1 < N1; ++k1) lds[(c * N1 + k1) * S::P2 + q] = x[k1];
     }
@@ -527,59 +567,62 @@ __device__ __forceinline__ void mr_r2c_body(const MrX<T> &t) {
     __syncthreads();
     // split Z = A + i B into the half spectra of the two lines, row by row:
     // mode (kb, cc, kk), lanes along the C modes of a row
-    const int total = t.nkb * C * S::XP;
+    constexpr int total = S::NKB * C * S::XP;
     const T h = T(0.5);
-    for (int f = tid; f < total; f += S::XTHREADS) {
+    for (int f = tid; f < total; f += NT) {
         const int kk = f & (C - 1), cc = (f / C) & (S::XP - 1), kb = f / (C * S::XP);
         const int k = kb * C + kk;
-        const long long ga = t.g0 + 2 * cc;
-        if (k < t.nxh && ga < t.lines) {
+        const unsigned ga = g0 + 2 * cc;
+        if (k < S::NXH && ga < lines) {
             const cx<T> z = lds[cc * S::SP + k];
             const cx<T> w = lds[cc * S::SP + (k == 0 ? 0 : N - k)];
-            const long long o = kb * t.kbstride + kk;
-            mr_st<T>(t.out_c + rowoff[2 * cc] + o, cmk<T>((z.x + w.x) * h, (z.y - w.y) * h));
-            if (ga + 1 < t.lines)
-                mr_st<T>(t.out_c + rowoff[2 * cc + 1] + o, cmk<T>((z.y + w.y) * h, (w.x - z.x) * h));
+            const unsigned o = kb * a.x.kbrows;  // rows of 128 bytes
+            mr_st<T>(out, (row[2 * cc] + o) * 128 + kk * CS, cmk<T>((z.x + w.x) * h, (z.y - w.y) * h));
+            if (ga + 1 < lines)
+                mr_st<T>(out, (row[2 * cc + 1] + o) * 128 + kk * CS, cmk<T>((z.y + w.y) * h, (w.x - z.x) * h));
         }
     }
 }
 
 // backward: half spectra in the blocked workspace -> real lines
-template <typename T, int N1, int N2>
-__device__ __forceinline__ void mr_c2r_body(const MrX<T> &t) {
+template <typename T, int N1, int N2, int NT>
+__device__ __forceinline__ void mr_c2r_body(const MrArgs &a, unsigned tile, unsigned *row) {
     using S = MrShape<T, N1, N2>;
     constexpr int N = S::N, C = S::C;
     constexpr int EH = 4;  // rows in flight per thread before the LDS writes
-    __shared__ long long rowoff[2 * S::XP];
+    constexpr unsigned CS = sizeof(cx<T>), RS = sizeof(T);
     cx<T> *lds = reinterpret_cast<cx<T> *>(pf_smem);
     const int tid = threadIdx.x;
-    mr_rowoff<T, S::XP>(t, rowoff);
+    const unsigned g0 = tile * (2 * S::XP), lines = a.x.lines;
+    const cx<T> *tw = reinterpret_cast<const cx<T> *>(a.tw);
+    const cx<T> *in = reinterpret_cast<const cx<T> *>(a.in) + mr_rows<T, S::XP>(a, g0, row) * C;
+    T *out = reinterpret_cast<T *>(a.out) + (size_t)g0 * N;
     __syncthreads();
     // conj(Z), Z = A + i B, on the whole line: modes k < nxh from the rows, the
     // rest by Hermitian symmetry; the imaginary parts of modes 0 and N / 2 are
     // dropped
-    const int total = t.nkb * C * S::XP;
-    for (int f1 = tid; f1 < total; f1 += EH * S::XTHREADS) {
+    constexpr int total = S::NKB * C * S::XP;
+    for (int f1 = tid; f1 < total; f1 += EH * NT) {
         cx<T> ra[EH], rb[EH];
 #pragma unroll
         for (int i = 0; i < EH; ++i) {
             ra[i] = rb[i] = cmk<T>(T(0), T(0));
-            const int f = f1 + i * S::XTHREADS;
+            const int f = f1 + i * NT;
             const int kk = f & (C - 1), cc = (f / C) & (S::XP - 1), kb = f / (C * S::XP);
             const int k = kb * C + kk;
-            const long long ga = t.g0 + 2 * cc;
-            if (f < total && k < t.nxh && ga < t.lines) {
-                const long long o = kb * t.kbstride + kk;
-                ra[i] = mr_ld<T>(t.in_c + rowoff[2 * cc] + o);
-                if (ga + 1 < t.lines) rb[i] = mr_ld<T>(t.in_c + rowoff[2 * cc + 1] + o);
+            const unsigned ga = g0 + 2 * cc;
+            if (f < total && k < S::NXH && ga < lines) {
+                const unsigned o = kb * a.x.kbrows;  // rows of 128 bytes
+                ra[i] = mr_ld<T>(in, (row[2 * cc] + o) * 128 + kk * CS);
+                if (ga + 1 < lines) rb[i] = mr_ld<T>(in, (row[2 * cc + 1] + o) * 128 + kk * CS);
             }
         }
 #pragma unroll
         for (int i = 0; i < EH; ++i) {
-            const int f = f1 + i * S::XTHREADS;
+            const int f = f1 + i * NT;
             const int kk = f & (C - 1), cc = (f / C) & (S::XP - 1), kb = f / (C * S::XP);
             const int k = kb * C + kk;
-            if (f < total && k < t.nxh) {
+            if (f < total && k < S::NXH) {
                 const cx<T> A = ra[i], B = rb[i];
                 cx<T> *col = lds + cc * S::SP;
                 if (k == 0 || 2 * k == N) {
@@ -599,7 +642,7 @@ __device__ __forceinline__ void mr_c2r_body(const MrX<T> &t) {
         for (int m = 0; m < N1; ++m) x[m] = lds[c * S::SP + q + N2 * m];
         DftMR<T, N1>::run(x);
 #pragma unroll
-        for (int k1 = 1; k1 < N1; ++k1) x[k1] = cmul(x[k1], mr_ld<T>(t.tw + q * k1));
+        for (int k1 = 1; k1 < N1; ++k1) x[k1] = cmul(x[k1], mr_ld<T>(tw, q * k1 * CS));
     }
     __syncthreads();  // the lines are read before the exchange tile overwrites them
     if (tid < S::XP * N2) {
@@ -613,69 +656,45 @@ __device__ __forceinline__ void mr_c2r_body(const MrX<T> &t) {
 #pragma unroll
         for (int n2 = 0; n2 < N2; ++n2) y[n2] = lds[(c2 * N1 + k1) * S::P2 + n2];
         DftMR<T, N2>::run(y);
-        const long long ga = t.g0 + 2 * c2;
-        if (ga < t.lines) {
-            T *pa = t.out_r + ga * t.ld_real + k1;
+        const unsigned ga = g0 + 2 * c2;
+        if (ga < lines) {
 #pragma unroll
-            for (int k2 = 0; k2 < N2; ++k2) mr_st1(pa + N1 * k2, y[k2].x);
+            for (int k2 = 0; k2 < N2; ++k2) mr_st1<T>(out, (2 * c2 * N + k1 + N1 * k2) * RS, y[k2].x);
         }
-        if (ga + 1 < t.lines) {
-            T *pb = t.out_r + (ga + 1) * t.ld_real + k1;
+        if (ga + 1 < lines) {
 #pragma unroll
-            for (int k2 = 0; k2 < N2; ++k2) mr_st1(pb + N1 * k2, -y[k2].y);
+            for (int k2 = 0; k2 < N2; ++k2) mr_st1<T>(out, ((2 * c2 + 1) * N + k1 + N1 * k2) * RS, -y[k2].y);
         }
     }
 }
 
 // ---- kernels: one tile per workgroup, a plan's pass or a batch's ------------------
-// MrArgs.b.count == 0: the plan's pass arguments `one`; else the batch work
-// list b (transforms of this one length).
-struct MrArgs {
-    PassArgs one;
-    BatchArgs b;
-    int dir;  // C2C: -1 forward, +1 backward
-};
-
-__device__ __forceinline__ int mr_find(const BatchArgs &b, long long blk) {
-    int lo = 0, hi = b.count - 1;
-    while (lo < hi) {
-        const int mid = (lo + hi + 1) >> 1;
-        if (b.first[mid] <= blk) lo = mid;
-        else hi = mid - 1;
+// C2C of a plan: grid (column blocks, outer indices); the others: grid (tiles).
+template <typename T, int N1, int N2, int CT>
+__device__ __forceinline__ void mr_c2c_tile(const MrArgs &m, const MrArgs &a, unsigned tile) {
+    unsigned cb = tile, ta = blockIdx.y;
+    if (m.flags & MR_BATCH) {
+        ta = tile / (unsigned)a.CB;
+        cb = tile - ta * (unsigned)a.CB;
     }
-    return lo;
+    mr_c2c_body<T, N1, N2, CT>(a, ta, cb);
 }
 
 template <int N1, int N2, typename T>
 __global__ __launch_bounds__(mr_c2c_threads<T>(N1, N2)) void k_mr_c2c(MrArgs m) {
-    const long long blk = blockIdx.x;
-    MrC2C<T> t;
-    if (m.b.count == 0) {
-        t = mr_c2c_args<T>(m.one, m.dir, m.one.in, m.one.out, blk);
-    } else {
-        const int i = mr_find(m.b, blk);
-        const PassArgs &a = m.b.args[i];
-        t = mr_c2c_args<T>(a, m.dir, m.b.in_user ? (const void *)(m.b.user_in + (size_t)a.in) : a.in,
-                           m.b.out_user ? (void *)(m.b.user_out + (size_t)a.out) : a.out, blk - m.b.first[i]);
-    }
-    mr_c2c_body<T, N1, N2>(t);
+    MrArgs a;
+    const unsigned tile = mr_resolve(m, a);
+    mr_c2c_tile<T, N1, N2, mr_c2c_cols<T>(N1, N2)>(m, a, tile);
 }
 
 template <int N1, int N2, int FWD, typename T>
 __global__ __launch_bounds__(mr_x_threads<T>(N1, N2)) void k_mr_x(MrArgs m) {
-    const long long blk = blockIdx.x;
-    constexpr int XP = MrShape<T, N1, N2>::XP;
-    MrX<T> t;
-    if (m.b.count == 0) {
-        t = mr_x_args<T>(m.one, m.one.in, m.one.out, blk, XP);
-    } else {
-        const int i = mr_find(m.b, blk);
-        const PassArgs &a = m.b.args[i];
-        t = mr_x_args<T>(a, m.b.in_user ? (const void *)(m.b.user_in + (size_t)a.in) : a.in,
-                         m.b.out_user ? (void *)(m.b.user_out + (size_t)a.out) : a.out, blk - m.b.first[i], XP);
-    }
-    if constexpr (FWD) mr_r2c_body<T, N1, N2>(t);
-    else mr_c2r_body<T, N1, N2>(t);
+    MrArgs a;
+    const unsigned tile = mr_resolve(m, a);
+    constexpr int NT = mr_x_threads<T>(N1, N2);
+    __shared__ unsigned row[kMrRows];
+    if constexpr (FWD) mr_r2c_body<T, N1, N2, NT>(a, tile, row);
+    else mr_c2r_body<T, N1, N2, NT>(a, tile, row);
 }
 
 // Lengths with a compile-time plan and their factors N1 <= N2, the pair
@@ -733,6 +752,82 @@ const void *mr_kernel_at(int what) {
         case MR_C2R: return reinterpret_cast<const void *>(&k_mr_x<N1, N2, 0, T>);
     }
     return nullptr;
+}
+
+// ---- batched launches over several lengths -------------------------------------------
+// One kernel per class of lengths (kMrLen positions first .. last - 1): the
+// workgroups of every transform of the class in one launch, each branching to
+// its length's code.  A launch per length (25 lengths in a batch of 32 grids: 144
+// launches a pair of 5 .. 60 us, most with fewer tiles than would fill the
+// chip) left the device to the tails; the classes keep lengths of similar
+// register, LDS and thread needs together.  Measured per pair, a launch per
+// length -> per class: 32 FP32 grids of 48 .. 320 points 2.04 -> 1.38 ms, 15 FP64
+// grids of 24 .. 124 points 0.357 -> 0.147 ms.
+struct MrClass {
+    int first, last, cap;  // positions; threads per column (items beyond go to a second round)
+};
+constexpr MrClass kMrClass[] = {{0, 36, 16}, {36, 60, 16}, {60, 72, 20}};  // 16 .. 112, 120 .. 243, 245 .. 324
+constexpr int kMrClasses = (int)(sizeof(kMrClass) / sizeof(kMrClass[0]));
+
+constexpr int mr_class(int index) {
+    for (int c = 0; c < kMrClasses; ++c)
+        if (index >= kMrClass[c].first && index < kMrClass[c].last) return c;
+    return -1;
+}
+template <typename T>
+constexpr int mr_class_cols(int c) {  // threads per column: whole waves
+    const int w = 64 / mr_cols<T>();
+    return (kMrClass[c].cap + w - 1) / w * w;
+}
+template <typename T>
+constexpr int mr_class_c2c_threads(int c) {
+    return mr_cols<T>() * mr_class_cols<T>(c);
+}
+template <typename T>
+constexpr int mr_class_x_threads(int c) {
+    int t = 0;
+    for (int i = kMrClass[c].first; i < kMrClass[c].last; ++i) {
+        const int x = mr_x_threads<T>(kMrLen[i].n1, kMrLen[i].n2);
+        t = x > t ? x : t;
+    }
+    return t;
+}
+
+// a.count of a batch entry: the transform's position in its class
+template <typename T, int CLS, int... I>
+__device__ __forceinline__ void mr_merged_c2c(const MrArgs &m, const MrArgs &a, unsigned tile,
+                                              std::integer_sequence<int, I...>) {
+    constexpr int F = kMrClass[CLS].first;
+    (void)((a.count == I
+                ? (mr_c2c_tile<T, kMrLen[F + I].n1, kMrLen[F + I].n2, mr_class_cols<T>(CLS)>(m, a, tile), true)
+                : false) || ...);
+}
+template <typename T, int CLS, int FWD, int... I>
+__device__ __forceinline__ void mr_merged_x(const MrArgs &a, unsigned tile, unsigned *row,
+                                            std::integer_sequence<int, I...>) {
+    constexpr int F = kMrClass[CLS].first, NT = mr_class_x_threads<T>(CLS);
+    auto one = [&](auto pos) {
+        constexpr int P = F + decltype(pos)::value;
+        if constexpr (FWD) mr_r2c_body<T, kMrLen[P].n1, kMrLen[P].n2, NT>(a, tile, row);
+        else mr_c2r_body<T, kMrLen[P].n1, kMrLen[P].n2, NT>(a, tile, row);
+        return true;
+    };
+    (void)((a.count == I ? one(std::integral_constant<int, I>()) : false) || ...);
+}
+
+template <int CLS, typename T>
+__global__ __launch_bounds__(mr_class_c2c_threads<T>(CLS)) void k_mr_c2c_class(MrArgs m) {
+    MrArgs a;
+    const unsigned tile = mr_resolve(m, a);
+    mr_merged_c2c<T, CLS>(m, a, tile, std::make_integer_sequence<int, kMrClass[CLS].last - kMrClass[CLS].first>());
+}
+template <int CLS, int FWD, typename T>
+__global__ __launch_bounds__(mr_class_x_threads<T>(CLS)) void k_mr_x_class(MrArgs m) {
+    MrArgs a;
+    const unsigned tile = mr_resolve(m, a);
+    __shared__ unsigned row[kMrRows];
+    mr_merged_x<T, CLS, FWD>(a, tile, row,
+                             std::make_integer_sequence<int, kMrClass[CLS].last - kMrClass[CLS].first>());
 }
 
 }  // namespace pf

@@ -14,7 +14,30 @@ PF_MR_EACH_UNIT(PF_MR_DECLARE, float)
 PF_MR_EACH_UNIT(PF_MR_DECLARE, double)
 #undef PF_MR_DECLARE
 
+// the batched kernels of the classes of lengths (kernels_mr_class.hip)
+static_assert(kMrClasses == 3, "every class is named below");
+#define PF_MR_EACH_CLASS(X, T) X(T, 0) X(T, 1) X(T, 2)
+#define PF_MR_DECLARE(T, U) const void *mr_class_##T##_##U(int what);
+PF_MR_EACH_CLASS(PF_MR_DECLARE, float)
+PF_MR_EACH_CLASS(PF_MR_DECLARE, double)
+#undef PF_MR_DECLARE
+
 namespace {
+
+template <typename T, int... C>
+unsigned class_threads(int cls, bool x, std::integer_sequence<int, C...>) {
+    static constexpr int c2c[] = {mr_class_c2c_threads<T>(C)...}, xs[] = {mr_class_x_threads<T>(C)...};
+    return (unsigned)(x ? xs[cls] : c2c[cls]);
+}
+
+const void *class_kernel(int cls, int prec, int what) {
+#define PF_MR_REF(T, U) mr_class_##T##_##U,
+    typedef const void *(*fn)(int);
+    static const fn f32[] = {PF_MR_EACH_CLASS(PF_MR_REF, float)};
+    static const fn f64[] = {PF_MR_EACH_CLASS(PF_MR_REF, double)};
+#undef PF_MR_REF
+    return (prec ? f64 : f32)[cls](what);
+}
 
 struct MrSizes {  // launch shape of one length in one precision
     int c2c_threads, x_threads, x_pairs;
@@ -50,13 +73,45 @@ int what_of(int kind) {
     return kind == PASS_C2C_MR ? MR_C2C : kind == PASS_R2C_MR ? MR_R2C : kind == PASS_C2R_MR ? MR_C2R : -1;
 }
 
-hipError_t mr_go(int kind, int n, int prec, unsigned blocks, unsigned threads, size_t lds, MrArgs &m, hipStream_t s) {
-    const int what = what_of(kind);
-    const void *k = what < 0 ? nullptr : mr_kernel(n, prec, what);
+hipError_t mr_go(const void *k, dim3 grid, unsigned threads, size_t lds, MrArgs &m, hipStream_t s) {
     if (!k) return hipErrorInvalidValue;
-    if (blocks == 0) return hipSuccess;
+    if (grid.x == 0 || grid.y == 0) return hipSuccess;
     void *args[] = {&m};
-    return hipLaunchKernel(k, dim3(blocks), dim3(threads), args, lds, s);
+    return hipLaunchKernel(k, grid, dim3(threads), args, lds, s);
+}
+
+// One side of a C2C pass: rows (columns contiguous; the workspace's, one block of
+// columns apart, or the user's) or lines (points contiguous).
+void pack_side(const Side &d, int cols, unsigned *sa, unsigned *sb, unsigned *ss, bool *lines) {
+    *lines = d.sp == 1 && d.sc != 1;
+    *sa = (unsigned)d.sa;
+    *sb = (unsigned)(d.cpb == 1 ? d.sblk : cols * d.sc);
+    *ss = (unsigned)(*lines ? d.sc : d.sp);
+}
+
+static_assert(sizeof(MrArgs) <= sizeof(PassArgs), "packed records fit the slots of the table");
+
+MrArgs pack(int kind, int dir, int prec, const PassArgs &a) {
+    MrArgs m;
+    std::memset(&m, 0, sizeof(m));
+    m.in = a.in;
+    m.out = a.out;
+    m.tw = a.tw;
+    if (kind == PASS_C2C_MR) {
+        bool il, ol;
+        const int cols = prec ? 8 : 16;
+        pack_side(a.in_s, cols, &m.c.isa, &m.c.isb, &m.c.iss, &il);
+        pack_side(a.out_s, cols, &m.c.osa, &m.c.osb, &m.c.oss, &ol);
+        m.C = a.C;
+        m.CB = (int)a.CB;
+        m.flags = (dir > 0 ? MR_BACKWARD : 0u) | (il ? MR_IN_LINES : 0u) | (ol ? MR_OUT_LINES : 0u);
+    } else {
+        m.x.zrows = (unsigned)a.zrows, m.x.kbrows = (unsigned)a.kbrows, m.x.y0 = (unsigned)a.y0;
+        m.x.ny = (unsigned)a.ny, m.x.lines = (unsigned)a.lines;
+    }
+    const int i = mr_index(a.fft.n), cls = i < 0 ? -1 : mr_class(i);
+    if (cls >= 0) m.count = i - kMrClass[cls].first;  // read from batch entries alone
+    return m;
 }
 
 }  // namespace
@@ -66,6 +121,11 @@ bool mr_supported(int n, int prec) { return (prec == 0 || prec == 1) && mr_index
 int mr_threads_of(int n, int prec, int xpass) {
     const int i = mr_index(n);
     return i < 0 ? 0 : xpass ? sizes(i, prec).x_threads : sizes(i, prec).c2c_threads;
+}
+
+int mr_long_factor(int n) {
+    const int i = mr_index(n);
+    return i < 0 ? 0 : kMrLen[i].n2;
 }
 
 int mr_x_pairs(int n, int prec) {
@@ -90,21 +150,42 @@ hipError_t mr_prepare(int n, int prec, int xpass) {
     return e;
 }
 
+int mr_batch_class(int n) {
+    const int i = mr_index(n);
+    return i < 0 ? -1 : mr_class(i);
+}
+
+size_t mr_entry_bytes() { return sizeof(MrArgs); }
+
+void mr_entry(int kind, int dir, int prec, const PassArgs &a, void *dst) {
+    const MrArgs m = pack(kind, dir, prec, a);
+    std::memcpy(dst, &m, sizeof(m));
+}
+
 hipError_t mr_launch(const PassDesc &d, hipStream_t s) {
-    MrArgs m;
-    std::memset(&m, 0, sizeof(m));
-    m.one = d.a;
-    m.dir = d.dir;
-    return mr_go(d.kind, d.a.fft.n, d.prec, d.blocks, d.threads, d.lds, m, s);
+    MrArgs m = pack(d.kind, d.dir, d.prec, d.a);
+    const dim3 grid = d.kind == PASS_C2C_MR ? dim3((unsigned)d.a.CB, (unsigned)d.a.A) : dim3(d.blocks);
+    const int what = what_of(d.kind);
+    return mr_go(what < 0 ? nullptr : mr_kernel(d.a.fft.n, d.prec, what), grid, d.threads, d.lds, m, s);
 }
 
 hipError_t mr_launch_batch(const BatchLaunch &L, hipStream_t s) {
+    if (L.b.count < 1) return hipErrorInvalidValue;
     MrArgs m;
     std::memset(&m, 0, sizeof(m));
-    m.b = L.b;
-    m.dir = L.dir;
-    if (m.b.count < 1) return hipErrorInvalidValue;
-    return mr_go(L.kind, L.n, L.prec, L.blocks, L.threads, L.lds, m, s);
+    m.in = L.b.user_in;
+    m.out = L.b.user_out;
+    m.b.table = reinterpret_cast<const MrArgs *>(L.b.args);
+    m.b.first = L.b.first;
+    m.count = L.b.count;
+    m.flags = MR_BATCH | (L.b.in_user ? MR_IN_USER : 0u) | (L.b.out_user ? MR_OUT_USER : 0u);
+    const int what = what_of(L.kind);
+    if (what < 0) return hipErrorInvalidValue;
+    if (L.cls < 0) return mr_go(mr_kernel(L.n, L.prec, what), dim3(L.blocks), L.threads, L.lds, m, s);
+    constexpr auto seq = std::make_integer_sequence<int, kMrClasses>();
+    const bool x = what != MR_C2C;
+    const unsigned threads = L.prec ? class_threads<double>(L.cls, x, seq) : class_threads<float>(L.cls, x, seq);
+    return mr_go(class_kernel(L.cls, L.prec, what), dim3(L.blocks), threads, L.lds, m, s);
 }
 
 }  // namespace pf

@@ -138,10 +138,11 @@ struct PassDesc {
     PassArgs a;
 };
 
-// Work list of one batched pass (generic kernels): transform i owns blocks
-// first[i] .. first[i+1] - 1 and runs with args[i] (device tables).  in_user /
-// out_user: the pass reads / writes the caller's arrays, and args[i].in /
-// .out hold byte offsets from user_in / user_out.
+// Work list of one batched pass: transform i owns blocks first[i] .. first[i+1] - 1
+// and runs with args[i] (device tables; mixed-radix passes: packed mr_entry
+// records from args on).  in_user / out_user: the pass reads / writes the
+// caller's arrays, and args[i].in / .out hold byte offsets from user_in /
+// user_out.
 struct BatchArgs {
     const PassArgs *args;
     const long long *first;
@@ -154,7 +155,8 @@ struct BatchArgs {
 struct BatchLaunch {
     PassKind kind;
     int dir, prec;
-    int n;  // mixed-radix passes: the transform length shared by the launch's transforms
+    int n;    // mixed-radix passes: the transform length shared by the launch's transforms,
+    int cls;  // or (>= 0) their class of lengths
     unsigned blocks, threads;
     size_t lds;
     BatchArgs b;
@@ -216,11 +218,17 @@ hipError_t p2_fused_launch(const FusedArgs &f, int fwd, int nx, int ny, unsigned
 // length n the table holds; one tile per workgroup.  a.tw: W_n^m, m < n
 // (forward sign).
 bool mr_supported(int n, int prec);
+int mr_long_factor(int n);                      // N2 of n = N1 N2 (0: not in the table)
 int mr_threads_of(int n, int prec, int xpass);  // threads per workgroup of the C2C (xpass 0) or X kernel
 int mr_x_pairs(int n, int prec);                // line pairs per X tile (a power of two)
 size_t mr_lds_bytes(int n, int prec, int xpass);
 hipError_t mr_prepare(int n, int prec, int xpass);  // allow the kernels their dynamic LDS
 hipError_t mr_launch(const PassDesc &d, hipStream_t s);
+// Class of lengths whose transforms share a batched launch (BatchLaunch.cls), -1: a launch per length.
+int mr_batch_class(int n);
+// One transform's entry (mr_entry_bytes() bytes, smaller than PassArgs) of a batched launch's table.
+size_t mr_entry_bytes();
+void mr_entry(int kind, int dir, int prec, const PassArgs &a, void *dst);
 hipError_t mr_launch_batch(const BatchLaunch &L, hipStream_t s);
 
 // Power-of-two FP64 C2C pass (kernels_p2.hip, k_c2c_p2d): plain FFT along Y or
