@@ -394,7 +394,9 @@ int pf_get_timing(pf_plan *p, int dir, int pass, double *total_ms, long long *co
  * in, out: real [nz][ny][nx]; spec: complex Z-pencil buffer of the plan
  * (caller-owned scratch, contents unspecified on return).  All distinct
  * (PF_EALIAS), 16-byte aligned.  PF_EUNSUPPORTED for other plans.
- * FP32 plans whose extension length 2 (nz - 1) is 256 .. 4096 run the z part
+ * FP32 plans whose extension length 2 (nz - 1) is a power of two from 256 to
+ * 4096, and plans of either precision where it has a compile-time mixed-radix
+ * plan (7-smooth, 16 .. 1024 but 686), run the z part
  * (forward DCT, product, backward DCT, and the adjoint's weights, which act
  * along z only and commute with the X and Y stages) as one pass on the
  * plan's workspace; the spectrum is then never written to spec.

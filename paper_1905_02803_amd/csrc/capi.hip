@@ -94,6 +94,10 @@ struct pf_plan {
     // the spectral step's Z passes and product fused into one pass on W
     bool spec_fused;
     PassDesc spec;
+    // the same for every other extension length with a compile-time mixed-radix
+    // plan (its table at tw_spec), FP32 and FP64
+    bool spec_mr;
+    size_t tw_spec;
     // fused X-Y passes (pf_layout.fused_xy): their arguments per direction
     // and the device counters they share (queue tickets, plane counts, status)
     bool fused;
@@ -779,6 +783,15 @@ void build_passes(pf_plan *p) {
         }
         p->npass[dir] = 3;
         if (p->blocked) add_remaps(p, dir);
+        if (dir == 0 && p->spec_mr) {
+            std::memset(&p->spec, 0, sizeof(p->spec));
+            p->spec.prec = p->lay.precision;
+            p->spec.a.fft = fz;
+            p->spec.a.tw = (const char *)p->tw_dev + p->tw_spec;
+            p->spec.a.A = p->ny;
+            p->spec.a.CB = p->nkb;
+            p->spec.a.in_s = ws_side(p, p->B, zstride, p->b_log2);
+        }
         if (dir == 0 && cheb && z.kind == pf::PASS_C2C_P2 && p->lay.precision == PF_F32 && !p->blocked && !p->share) {
             // fused spectral step: the forward Z pass's tiles, W on both sides (on the
             // transposed workspace: its rows of 16 ky at one kx, and a.xtr = 1)
@@ -1015,17 +1028,39 @@ int pf_query_dims(int nx, int ny, int nz, const pf_layout *l, int pencil, int r1
     return PF_OK;
 }
 
+}  // extern "C"
+
+namespace {
+
+// W_n^m = exp(-2 pi i m / n), m < n, appended to host in precision R (rounded once).
+template <typename R>
+void add_roots(int n, std::vector<unsigned char> &host) {
+    std::vector<R> t(2 * (size_t)n);
+    const double two_pi = 6.283185307179586476925286766559;
+    for (int m = 0; m < n; ++m) {
+        const double ang = two_pi * (double)m / (double)n;
+        t[2 * (size_t)m] = (R)std::cos(ang);
+        t[2 * (size_t)m + 1] = (R)(-std::sin(ang));
+    }
+    const unsigned char *b = reinterpret_cast<const unsigned char *>(t.data());
+    host.insert(host.end(), b, b + t.size() * sizeof(R));
+}
+
 // The mixed-radix kernels address one tile by 32-bit byte offsets from its base:
 // whether every tile of axis i stays below 4 GB.  X: the lines of a tile lie in
 // at most 31 / ny + 2 planes of the workspace; Z: a step reaches over N2 planes (of
 // the workspace or of [nz][ny][nxh], which is no larger), or over 16 lines ny nz
 // apart; Y tiles lie in one plane, and need only that to be below 4 GB.
-static bool mr_fits(const pf_plan *p, int i) {
+bool mr_fits(const pf_plan *p, int i) {
     const unsigned long long lim = 1ULL << 32, plane = (unsigned long long)p->zrows * 128;
     if (i == 0) return (31 / p->ny + 2) * plane < lim;
     if (i == 1) return plane < lim;
     return pf::mr_long_factor(p->nz) * plane < lim && 16ULL * p->ny * p->nz * p->csize < lim;
 }
+
+}  // namespace
+
+extern "C" {
 
 static int plan_create(int nx, int ny, int nz, const pf_layout *l, const PlanOpts &o, pf_plan **out) {
     if (!out) return PF_EINVAL;
@@ -1111,20 +1146,18 @@ static int plan_create(int nx, int ny, int nz, const pf_layout *l, const PlanOpt
         p->tw_mr[i] = 0;
         if (!p->mr[i]) continue;
         p->tw_mr[i] = host.size();
-        auto mr_table = [&](auto zero) {
-            typedef decltype(zero) R;
-            std::vector<R> t(2 * (size_t)axis_n[i]);
-            const double two_pi = 6.283185307179586476925286766559;
-            for (int m = 0; m < axis_n[i]; ++m) {
-                const double ang = two_pi * (double)m / (double)axis_n[i];
-                t[2 * (size_t)m] = (R)std::cos(ang);
-                t[2 * (size_t)m + 1] = (R)(-std::sin(ang));
-            }
-            const unsigned char *b = reinterpret_cast<const unsigned char *>(t.data());
-            host.insert(host.end(), b, b + t.size() * sizeof(R));
-        };
-        if (l->precision == PF_F64) mr_table(0.0);
-        else mr_table(0.f);
+        if (l->precision == PF_F64) add_roots<double>(axis_n[i], host);
+        else add_roots<float>(axis_n[i], host);
+        host.resize((host.size() + 255) & ~(size_t)255, 0);
+    }
+    // (the fused step of the power-of-two kernels, FP32, goes first: p2_supported)
+    p->spec_mr = l->third == PF_THIRD_CHEB && !o.no_mr && !o.generic_only && !l->share_only && l->m1 * l->m2 == 1 &&
+                 !l->inplace && !l->fused_xy && pf::mr_supported(p->fz.n, l->precision) &&
+                 !pf::p2_supported(p->fz.n, l->precision) && (unsigned long long)nz * p->zrows * 128 < (1ULL << 32);
+    p->tw_spec = host.size();
+    if (p->spec_mr) {
+        if (l->precision == PF_F64) add_roots<double>(p->fz.n, host);
+        else add_roots<float>(p->fz.n, host);
         host.resize((host.size() + 255) & ~(size_t)255, 0);
     }
     // the split type-I DCT of the fused spectral step (FP32, nz = L + 1 = 257)
@@ -1169,6 +1202,7 @@ static int plan_create(int nx, int ny, int nz, const pf_layout *l, const PlanOpt
     }
     for (int i = 0; i < 3; ++i)
         if (e == hipSuccess && p->mr[i]) e = pf::mr_prepare(axis_n[i], l->precision, i == 0);
+    if (e == hipSuccess && p->spec_mr) e = pf::mr_prepare(p->fz.n, l->precision, 0);
     const bool cheb_p2 = l->third == PF_THIRD_CHEB && !o.generic_only && pf::p2_supported(p->fz.n, l->precision);
     if (e == hipSuccess && cheb_p2) e = pf::p2_spec_prepare(p->fz.n);
     if (e == hipSuccess && p->fast_x) e = pf::p2x_prepare(nx, l->precision);
@@ -1428,7 +1462,7 @@ int pf_spectral_step(pf_plan *p, const void *in, void *spec, void *out, int adjo
     a.nx = p->nx, a.ny = p->ny, a.nz = p->nz, a.nxh = p->nxh, a.stride1 = p->lay.stride1, a.f64 = f64;
     a.conj = adjoint;
     a.scale = 1.0 / ((double)p->nx * p->ny * 2.0 * (p->nz - 1));
-    if (p->spec_fused) {  // X, Y forward; Z, product, Z in one pass on W; Y, X backward
+    if (p->spec_fused || p->spec_mr) {  // X, Y forward; Z, product, Z in one pass on W; Y, X backward
         int r = check_call(p, in, out);
         if (!r) r = run_one(p, 0, 0, in, p->ws, s);
         if (!r) r = run_one(p, 0, 1, p->ws, p->ws, s);
@@ -1436,7 +1470,8 @@ int pf_spectral_step(pf_plan *p, const void *in, void *spec, void *out, int adjo
             pf::PassDesc d = p->spec;
             d.a.in = p->ws;
             d.a.out = p->ws;
-            r = hip_status(pf::p2_spec_launch(d, adjoint, p->nx, (float)a.scale, s));
+            r = hip_status(p->spec_mr ? pf::mr_spec_launch(d.a, f64, adjoint, p->nx, s)
+                                      : pf::p2_spec_launch(d, adjoint, p->nx, (float)a.scale, s));
         }
         if (!r) r = run_one(p, 1, 1, p->ws, p->ws, s);
         if (!r) r = run_one(p, 1, 2, p->ws, out, s);

@@ -142,9 +142,11 @@ hipError_t mr_prepare(int n, int prec, int xpass) {
     const size_t lds = mr_lds_bytes(n, prec, xpass);
     if (lds <= 64 * 1024) return hipSuccess;  // the default limit
     hipError_t e = hipSuccess;
-    for (int what : {MR_C2C, MR_R2C, MR_C2R}) {
-        if ((what != MR_C2C) != (xpass != 0) || e != hipSuccess) continue;
+    for (int what : {MR_C2C, MR_R2C, MR_C2R, MR_SPEC}) {
+        const bool x = what == MR_R2C || what == MR_C2R;
+        if (x != (xpass != 0) || e != hipSuccess) continue;
         const void *k = mr_kernel(n, prec, what);
+        if (!k && what == MR_SPEC) continue;  // odd lengths have none
         e = k ? hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) : hipErrorInvalidValue;
     }
     return e;
@@ -167,6 +169,20 @@ hipError_t mr_launch(const PassDesc &d, hipStream_t s) {
     const dim3 grid = d.kind == PASS_C2C_MR ? dim3((unsigned)d.a.CB, (unsigned)d.a.A) : dim3(d.blocks);
     const int what = what_of(d.kind);
     return mr_go(what < 0 ? nullptr : mr_kernel(d.a.fft.n, d.prec, what), grid, d.threads, d.lds, m, s);
+}
+
+hipError_t mr_spec_launch(const PassArgs &a, int prec, int adj, int nx, hipStream_t s) {
+    const int n = a.fft.n;
+    MrArgs m;
+    std::memset(&m, 0, sizeof(m));
+    m.in = a.in;
+    m.out = a.out;
+    m.tw = a.tw;
+    m.s.sa = (unsigned)a.in_s.sa, m.s.sb = (unsigned)a.in_s.sblk, m.s.ss = (unsigned)a.in_s.sp;
+    m.s.nx = (unsigned)nx, m.s.ny = (unsigned)a.A;
+    m.flags = adj ? MR_BACKWARD : 0u;
+    return mr_go(mr_kernel(n, prec, MR_SPEC), dim3((unsigned)a.CB, (unsigned)a.A), (unsigned)mr_threads_of(n, prec, 0),
+                 mr_lds_bytes(n, prec, 0), m, s);
 }
 
 hipError_t mr_launch_batch(const BatchLaunch &L, hipStream_t s) {

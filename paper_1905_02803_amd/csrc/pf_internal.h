@@ -229,6 +229,9 @@ int mr_batch_class(int n);
 // One transform's entry (mr_entry_bytes() bytes, smaller than PassArgs) of a batched launch's table.
 size_t mr_entry_bytes();
 void mr_entry(int kind, int dir, int prec, const PassArgs &a, void *dst);
+// Spectral step along z in place on the workspace a.in_s at a.out (extension length
+// a.fft.n even and in the table, a.A = ny, a.CB column blocks, a.tw its table).
+hipError_t mr_spec_launch(const PassArgs &a, int prec, int adj, int nx, hipStream_t s);
 hipError_t mr_launch_batch(const BatchLaunch &L, hipStream_t s);
 
 // Power-of-two FP64 C2C pass (kernels_p2.hip, k_c2c_p2d): plain FFT along Y or
