@@ -339,8 +339,23 @@ void set_c2c_common(PassDesc &d, const pf_plan *p, const FftSpec &fs, size_t two
 #define PF_XCD_UROWS 1
 #endif
 
+// Mixed-radix passes that give each XCD runs of consecutive tiles: X and Y of a
+// workspace up to this size, where an XCD then finds in its own L2 (4 MB, 32 MB in
+// all) part of what it wrote in the pass before (pair, off -> on: FP32 100^3 29.3
+// -> 28.6 us, 150^3 58.7 -> 53.0, 196^3, 49 MB, 85.0 -> 81.6; FP64 100^3 43.8 ->
+// 38.1; 250^3, 128 MB, 154 -> 156 and 384^3 594 -> 610), and every Z pass with a
+// side of [nz][ny][nxh] rows, whose 128-byte segments straddle cache lines that
+// neighbouring tiles share (FP32 384^3 677 -> 627 us, FP64 300 x 280 x 250 451 ->
+// 400; on STRIDE1 lines it is slower: 768 x 768 x 384 forward Z 473 -> 530 us).
+constexpr size_t kXcdRunBytes = (size_t)64 << 20;
+
 unsigned c2c_grid(const pf_plan *p, PassDesc &d) {
     const long long tiles = d.a.A * d.a.CB;
+    if (d.kind == pf::PASS_C2C_MR) {
+        // natural-order rows: columns contiguous, all column blocks in one row
+        auto rows = [p](const Side &s) { return !p->lay.stride1 && s.sc == 1 && s.sblk == 0; };
+        d.a.xcd = rows(d.a.in_s) || rows(d.a.out_s) || (d.a.in_s.sp == p->B && p->w_bytes <= kXcdRunBytes);
+    }
     if (d.kind != pf::PASS_C2C_P2) return (unsigned)tiles;
     // side kinds: 1 lines, 0 aligned rows, 2 rows read / written a column at a time
     d.a.inp = (d.a.in_s.sp == 1 && d.a.in_s.sc != 1) ? 1 : d.a.in_s.v8 ? 2 : 0;
@@ -668,6 +683,7 @@ void build_passes(pf_plan *p) {
             x.threads = (unsigned)pf::mr_threads_of(p->nx, x.prec, 1);
             x.lds = pf::mr_lds_bytes(p->nx, x.prec, 1);
             x.blocks = (unsigned)((pairs + xp - 1) / xp);
+            x.a.xcd = p->w_bytes <= kXcdRunBytes;
         }
         if (p->fast_x) {  // half-length complex transform, 16 (FP64: 8) lines per tile, persistent blocks
             x.kind = dir == 0 ? pf::PASS_R2C_P2 : pf::PASS_C2R_P2;

@@ -172,6 +172,11 @@ struct DftMR {
 #define PF_MR_SPLIT_ABOVE 81920
 #endif
 
+// Backward X kernel: 16-byte row accesses of each line in flight per thread (all
+// of them up to 8; 4 of 8 bytes measured 3.79 TB/s at 1000 points, 8 of 16 bytes
+// 4.41; 768 points 4.09 -> 4.52)
+constexpr int kMrRowLoads = 8;
+
 // columns of one C2C tile: a 128-byte workspace row
 template <typename T>
 __host__ __device__ constexpr int mr_cols() {
@@ -269,6 +274,22 @@ __device__ __forceinline__ void mr_st(void *base, unsigned off, cx<T> v) {
     const v2 u = {v.x, v.y};
     *(PF_GLOBAL v2 *)((PF_GLOBAL char *)base + off) = u;
 }
+// 16 bytes, aligned: two FP32 values or one FP64 value
+template <typename T>
+__device__ __forceinline__ void mr_ld16(const void *base, unsigned off, cx<T> (&v)[16 / sizeof(cx<T>)]) {
+    typedef T vv __attribute__((ext_vector_type(16 / sizeof(T))));
+    const vv u = *(const PF_GLOBAL vv *)((const PF_GLOBAL char *)base + off);
+#pragma unroll
+    for (int i = 0; i < (int)(16 / sizeof(cx<T>)); ++i) v[i] = cmk<T>(u[2 * i], u[2 * i + 1]);
+}
+template <typename T>
+__device__ __forceinline__ void mr_st16(void *base, unsigned off, const cx<T> (&v)[16 / sizeof(cx<T>)]) {
+    typedef T vv __attribute__((ext_vector_type(16 / sizeof(T))));
+    vv u;
+#pragma unroll
+    for (int i = 0; i < (int)(16 / sizeof(cx<T>)); ++i) u[2 * i] = v[i].x, u[2 * i + 1] = v[i].y;
+    *(PF_GLOBAL vv *)((PF_GLOBAL char *)base + off) = u;
+}
 template <typename T>
 __device__ __forceinline__ void mr_st1(void *base, unsigned off, T v) {
     *(PF_GLOBAL T *)((PF_GLOBAL char *)base + off) = v;
@@ -281,7 +302,8 @@ __device__ __forceinline__ void mr_st1(void *base, unsigned off, T v) {
 // pass by 0.4 us (FP64 64^3 replayed from a graph 24.7 -> 22.2 us per pair).
 // Strides are in elements; every one of a
 // grid up to 8192^3 fits 32 bits.
-enum : unsigned { MR_BACKWARD = 1, MR_IN_LINES = 2, MR_OUT_LINES = 4, MR_BATCH = 8, MR_IN_USER = 16, MR_OUT_USER = 32 };
+enum : unsigned { MR_BACKWARD = 1, MR_IN_LINES = 2, MR_OUT_LINES = 4, MR_BATCH = 8, MR_IN_USER = 16, MR_OUT_USER = 32,
+                MR_XCD = 64 };
 struct MrArgs {
     const void *in;
     void *out;
@@ -325,10 +347,18 @@ __device__ __forceinline__ int mr_find(const long long *first, int count, long l
     return lo;
 }
 
+// Workgroup b of a launch of n, dealt to XCD b mod 8: its tile, so that each XCD
+// works through n / 8 consecutive tiles (the last n mod 8 in place).
+__device__ __forceinline__ unsigned mr_xcd_tile(unsigned b, unsigned n) {
+    const unsigned per = n >> 3;
+    return b < per * 8 ? (b & 7) * per + (b >> 3) : b;
+}
+
 // The transform of this workgroup and its tile (returned): m itself, or the
 // batch entry with its pointers resolved.
 __device__ __forceinline__ unsigned mr_resolve(const MrArgs &m, MrArgs &a) {
     a = m;
+    if (m.flags & MR_XCD) return mr_xcd_tile(blockIdx.x, (unsigned)m.count);
     if (!(m.flags & MR_BATCH)) return blockIdx.x;
     const int i = mr_find(m.b.first, m.count, blockIdx.x);
     a = m.b.table[i];
@@ -690,21 +720,28 @@ __device__ __forceinline__ void mr_r2c_body(const MrArgs &a, unsigned tile, unsi
         for (int k2 = 0; k2 < N2; ++k2) lds[c2 * S::SP + k1 + N1 * k2] = y[k2];
     }
     __syncthreads();
-    // split Z = A + i B into the half spectra of the two lines, row by row:
-    // mode (kb, cc, kk), lanes along the C modes of a row
-    constexpr int total = S::NKB * C * S::XP;
+    // split Z = A + i B into the half spectra of the two lines, row by row: 16 bytes
+    // (V modes) per lane, 8 lanes along a row (kb, cc); the slots past the last
+    // mode of the last row block are written with what LDS holds
+    constexpr int V = C / 8, total = S::NKB * 8 * S::XP;
     const T h = T(0.5);
+#pragma unroll 4
     for (int f = tid; f < total; f += NT) {
-        const int kk = f & (C - 1), cc = (f / C) & (S::XP - 1), kb = f / (C * S::XP);
+        const int kk = (f & 7) * V, cc = (f / 8) & (S::XP - 1), kb = f / (8 * S::XP);
         const int k = kb * C + kk;
         const unsigned ga = g0 + 2 * cc;
         if (k < S::NXH && ga < lines) {
-            const cx<T> z = lds[cc * S::SP + k];
-            const cx<T> w = lds[cc * S::SP + (k == 0 ? 0 : N - k)];
+            cx<T> za[V], zb[V];
+#pragma unroll
+            for (int v = 0; v < V; ++v) {
+                const cx<T> z = lds[cc * S::SP + k + v];
+                const cx<T> w = lds[cc * S::SP + (k + v == 0 ? 0 : N - k - v)];
+                za[v] = cmk<T>((z.x + w.x) * h, (z.y - w.y) * h);
+                zb[v] = cmk<T>((z.y + w.y) * h, (w.x - z.x) * h);
+            }
             const unsigned o = kb * a.x.kbrows;  // rows of 128 bytes
-            mr_st<T>(out, (row[2 * cc] + o) * 128 + kk * CS, cmk<T>((z.x + w.x) * h, (z.y - w.y) * h));
-            if (ga + 1 < lines)
-                mr_st<T>(out, (row[2 * cc + 1] + o) * 128 + kk * CS, cmk<T>((z.y + w.y) * h, (w.x - z.x) * h));
+            mr_st16<T>(out, (row[2 * cc] + o) * 128 + kk * CS, za);
+            if (ga + 1 < lines) mr_st16<T>(out, (row[2 * cc + 1] + o) * 128 + kk * CS, zb);
         }
     }
 }
@@ -714,7 +751,6 @@ template <typename T, int N1, int N2, int NT>
 __device__ __forceinline__ void mr_c2r_body(const MrArgs &a, unsigned tile, unsigned *row) {
     using S = MrShape<T, N1, N2>;
     constexpr int N = S::N, C = S::C;
-    constexpr int EH = 4;  // rows in flight per thread before the LDS writes
     constexpr unsigned CS = sizeof(cx<T>), RS = sizeof(T);
     cx<T> *lds = reinterpret_cast<cx<T> *>(pf_smem);
     const int tid = threadIdx.x;
@@ -726,35 +762,39 @@ __device__ __forceinline__ void mr_c2r_body(const MrArgs &a, unsigned tile, unsi
     // conj(Z), Z = A + i B, on the whole line: modes k < nxh from the rows, the
     // rest by Hermitian symmetry; the imaginary parts of modes 0 and N / 2 are
     // dropped
-    constexpr int total = S::NKB * C * S::XP;
+    constexpr int V = C / 8, total = S::NKB * 8 * S::XP;  // 16 bytes (V modes) per lane
+    constexpr int ROUNDS = (total + NT - 1) / NT, EH = ROUNDS < kMrRowLoads ? ROUNDS : kMrRowLoads;
     for (int f1 = tid; f1 < total; f1 += EH * NT) {
-        cx<T> ra[EH], rb[EH];
+        cx<T> ra[EH][V], rb[EH][V];
 #pragma unroll
         for (int i = 0; i < EH; ++i) {
-            ra[i] = rb[i] = cmk<T>(T(0), T(0));
+#pragma unroll
+            for (int v = 0; v < V; ++v) ra[i][v] = rb[i][v] = cmk<T>(T(0), T(0));
             const int f = f1 + i * NT;
-            const int kk = f & (C - 1), cc = (f / C) & (S::XP - 1), kb = f / (C * S::XP);
-            const int k = kb * C + kk;
+            const int kk = (f & 7) * V, cc = (f / 8) & (S::XP - 1), kb = f / (8 * S::XP);
             const unsigned ga = g0 + 2 * cc;
-            if (f < total && k < S::NXH && ga < lines) {
+            if (f < total && kb * C + kk < S::NXH && ga < lines) {
                 const unsigned o = kb * a.x.kbrows;  // rows of 128 bytes
-                ra[i] = mr_ld<T>(in, (row[2 * cc] + o) * 128 + kk * CS);
-                if (ga + 1 < lines) rb[i] = mr_ld<T>(in, (row[2 * cc + 1] + o) * 128 + kk * CS);
+                mr_ld16<T>(in, (row[2 * cc] + o) * 128 + kk * CS, ra[i]);
+                if (ga + 1 < lines) mr_ld16<T>(in, (row[2 * cc + 1] + o) * 128 + kk * CS, rb[i]);
             }
         }
 #pragma unroll
         for (int i = 0; i < EH; ++i) {
             const int f = f1 + i * NT;
-            const int kk = f & (C - 1), cc = (f / C) & (S::XP - 1), kb = f / (C * S::XP);
-            const int k = kb * C + kk;
-            if (f < total && k < S::NXH) {
-                const cx<T> A = ra[i], B = rb[i];
-                cx<T> *col = lds + cc * S::SP;
-                if (k == 0 || 2 * k == N) {
-                    col[k] = cmk<T>(A.x, -B.x);
-                } else {
-                    col[k] = cmk<T>(A.x - B.y, -A.y - B.x);
-                    col[N - k] = cmk<T>(A.x + B.y, A.y - B.x);
+            const int kk = (f & 7) * V, cc = (f / 8) & (S::XP - 1), kb = f / (8 * S::XP);
+#pragma unroll
+            for (int v = 0; v < V; ++v) {
+                const int k = kb * C + kk + v;
+                if (f < total && k < S::NXH) {
+                    const cx<T> A = ra[i][v], B = rb[i][v];
+                    cx<T> *col = lds + cc * S::SP;
+                    if (k == 0 || 2 * k == N) {
+                        col[k] = cmk<T>(A.x, -B.x);
+                    } else {
+                        col[k] = cmk<T>(A.x - B.y, -A.y - B.x);
+                        col[N - k] = cmk<T>(A.x + B.y, A.y - B.x);
+                    }
                 }
             }
         }
@@ -798,7 +838,7 @@ __device__ __forceinline__ void mr_c2r_body(const MrArgs &a, unsigned tile, unsi
 template <typename T, int N1, int N2, int CT>
 __device__ __forceinline__ void mr_c2c_tile(const MrArgs &m, const MrArgs &a, unsigned tile) {
     unsigned cb = tile, ta = blockIdx.y;
-    if (m.flags & MR_BATCH) {
+    if (m.flags & (MR_BATCH | MR_XCD)) {
         ta = tile / (unsigned)a.CB;
         cb = tile - ta * (unsigned)a.CB;
     }

@@ -166,7 +166,12 @@ void mr_entry(int kind, int dir, int prec, const PassArgs &a, void *dst) {
 
 hipError_t mr_launch(const PassDesc &d, hipStream_t s) {
     MrArgs m = pack(d.kind, d.dir, d.prec, d.a);
-    const dim3 grid = d.kind == PASS_C2C_MR ? dim3((unsigned)d.a.CB, (unsigned)d.a.A) : dim3(d.blocks);
+    dim3 grid = d.kind == PASS_C2C_MR ? dim3((unsigned)d.a.CB, (unsigned)d.a.A) : dim3(d.blocks);
+    if (d.a.xcd) {
+        grid = dim3(grid.x * grid.y);
+        m.flags |= MR_XCD;
+        m.count = (int)grid.x;
+    }
     const int what = what_of(d.kind);
     return mr_go(what < 0 ? nullptr : mr_kernel(d.a.fft.n, d.prec, what), grid, d.threads, d.lds, m, s);
 }
