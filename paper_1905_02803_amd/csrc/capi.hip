@@ -349,6 +349,13 @@ void set_c2c_common(PassDesc &d, const pf_plan *p, const FftSpec &fs, size_t two
 // 400; on STRIDE1 lines it is slower: 768 x 768 x 384 forward Z 473 -> 530 us).
 constexpr size_t kXcdRunBytes = (size_t)64 << 20;
 
+// Backward mixed-radix Z pass of STRIDE1 plans on a workspace above this size:
+// neighbouring workgroups take neighbouring ky, whose lines and rows adjoin
+// (column blocks first -> ky first: FP32 768 x 768 x 384 422 -> 405 us, 384^3 116
+// -> 109, 320^3, 144 MB, 61 -> 57, FP64 600 x 400 x 450 375 -> 341; 250^3, 128 MB,
+// 29.2 -> 30.5; the forward pass 399 -> 429 at 600 x 400 x 450).
+constexpr size_t kOuterFastBytes = (size_t)128 << 20;
+
 unsigned c2c_grid(const pf_plan *p, PassDesc &d) {
     const long long tiles = d.a.A * d.a.CB;
     if (d.kind == pf::PASS_C2C_MR) {
@@ -727,6 +734,10 @@ void build_passes(pf_plan *p) {
         // walking column blocks first, so that neighbouring tiles (on one XCD)
         // share the cache lines the rows straddle
         z.a.tile_order = dir == 0 ? PF_TILE_ORDER_FZ : (p->lay.stride1 ? PF_TILE_ORDER_BZ : 0);
+        // mixed-radix: the backward pass from Z-pencil lines walks ky first above
+        // kOuterFastBytes
+        if (z.kind == pf::PASS_C2C_MR)
+            z.a.tile_order = dir == 1 && p->lay.stride1 && p->w_bytes > kOuterFastBytes ? 1 : 0;
         z.blocks = c2c_grid(p, z);
 
         if ((dir == 1 && p->bwd_tr) || (dir == 0 && p->fwd_tr)) {

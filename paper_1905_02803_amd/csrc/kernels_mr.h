@@ -303,7 +303,7 @@ __device__ __forceinline__ void mr_st1(void *base, unsigned off, T v) {
 // Strides are in elements; every one of a
 // grid up to 8192^3 fits 32 bits.
 enum : unsigned { MR_BACKWARD = 1, MR_IN_LINES = 2, MR_OUT_LINES = 4, MR_BATCH = 8, MR_IN_USER = 16, MR_OUT_USER = 32,
-                MR_XCD = 64 };
+                MR_XCD = 64, MR_OUTER_FAST = 128 };
 struct MrArgs {
     const void *in;
     void *out;
@@ -834,13 +834,17 @@ __device__ __forceinline__ void mr_c2r_body(const MrArgs &a, unsigned tile, unsi
 }
 
 // ---- kernels: one tile per workgroup, a plan's pass or a batch's ------------------
-// C2C of a plan: grid (column blocks, outer indices); the others: grid (tiles).
+// C2C of a plan: grid (column blocks, outer indices), with MR_OUTER_FAST (outer
+// indices, column blocks); the others: grid (tiles).
 template <typename T, int N1, int N2, int CT>
 __device__ __forceinline__ void mr_c2c_tile(const MrArgs &m, const MrArgs &a, unsigned tile) {
     unsigned cb = tile, ta = blockIdx.y;
     if (m.flags & (MR_BATCH | MR_XCD)) {
         ta = tile / (unsigned)a.CB;
         cb = tile - ta * (unsigned)a.CB;
+    } else if (m.flags & MR_OUTER_FAST) {
+        ta = tile;
+        cb = blockIdx.y;
     }
     mr_c2c_body<T, N1, N2, CT>(a, ta, cb);
 }

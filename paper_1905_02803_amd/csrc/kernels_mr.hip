@@ -171,6 +171,9 @@ hipError_t mr_launch(const PassDesc &d, hipStream_t s) {
         grid = dim3(grid.x * grid.y);
         m.flags |= MR_XCD;
         m.count = (int)grid.x;
+    } else if (d.kind == PASS_C2C_MR && d.a.tile_order) {
+        grid = dim3(grid.y, grid.x);
+        m.flags |= MR_OUTER_FAST;
     }
     const int what = what_of(d.kind);
     return mr_go(what < 0 ? nullptr : mr_kernel(d.a.fft.n, d.prec, what), grid, d.threads, d.lds, m, s);

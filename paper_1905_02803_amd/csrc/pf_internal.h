@@ -110,7 +110,7 @@ struct PassArgs {
                     // 3 (C2C pass) no transform: the reorder alone, 4 (C2C pass) type-I DCT by the
                     // even extension (lines of cheb = fft.n / 2 + 1 points), 5 (fused spectral
                     // step) type-I DCT split once
-    int tile_order; // power-of-two C2C pass: 0 tile t = (t / CB, t % CB), 1 tile t = (t % A, t / A)
+    int tile_order; // power-of-two and mixed-radix C2C pass: 0 tile t = (t / CB, t % CB), 1 tile t = (t % A, t / A)
     int xcd;        // power-of-two C2C and mixed-radix passes: 1 to give each XCD runs of consecutive tiles
     int cheb;       // C2C pass: > 0 = lines of cheb points, transformed as their even
                     // extension of length fft.n = 2 (cheb - 1) (type-I DCT); 0 = plain
