@@ -257,6 +257,15 @@ int built_options(int nx, int ny, const pf_layout *l) {
     return PF_OK;
 }
 
+// C2C passes up to this length take the mixed-radix kernel where the power-of-two
+// family has one too: 37 KB of LDS (FP32) and one tile per workgroup, so more of
+// them at once; 256^3 FP32 pass 26.6 us against 31.5 (pair 152 against 163), FP64
+// pair 313 against 337, 300 x 256 x 256 natural order 179 against 208.  FP64 on the
+// transposed workspace keeps the persistent kernel (512 x 256 x 256 603 us against
+// 608).  At 512 and 1024 the persistent kernel is the faster (600 x 1024 x 512 3069
+// us against 3246), and the matrix-core variants exist there only.
+constexpr int kMrBeforeP2 = 256;
+
 // The power-of-two kernel serves every side: the padded workspace (whole
 // 16-column blocks, 16-byte aligned rows), contiguous lines, and unaligned
 // rows (Side::v8).
@@ -270,7 +279,9 @@ void set_c2c_common(PassDesc &d, const pf_plan *p, const FftSpec &fs, size_t two
     a.fft = fs;
     a.tw = (const char *)p->tw_dev + twoff;
     a.C = p->nxh;
-    if (!p->opt.generic_only && pf::p2_supported(fs.n, p->lay.precision) && pf::p2_tc(fs.n) <= max_tc) {
+    const bool mr = axis >= 0 && p->mr[axis] && plain_fft && max_tc >= p->B;
+    const bool mr_first = mr && fs.n <= kMrBeforeP2 && !(p->lay.precision == PF_F64 && p->bwd_tr);
+    if (!mr_first && !p->opt.generic_only && pf::p2_supported(fs.n, p->lay.precision) && pf::p2_tc(fs.n) <= max_tc) {
         // compile-time radix plan, persistent blocks (grid set once the tile count is known)
         d.kind = pf::PASS_C2C_P2;
         a.math = pf::p2_has_mfma(fs.n) ? p->lay.math : 0;
@@ -280,7 +291,7 @@ void set_c2c_common(PassDesc &d, const pf_plan *p, const FftSpec &fs, size_t two
         d.lds = pf::p2_lds_bytes(fs.n, a.math);
         return;
     }
-    if (!p->opt.generic_only && p->lay.precision == PF_F64 && plain_fft && pf::p2d_supported(fs.n) &&
+    if (!mr_first && !p->opt.generic_only && p->lay.precision == PF_F64 && plain_fft && pf::p2d_supported(fs.n) &&
         p->B <= max_tc) {
         // FP64 compile-time radix plan: 8 columns (one 128-byte row) per tile, persistent blocks
         d.kind = pf::PASS_C2C_P2;
@@ -291,7 +302,7 @@ void set_c2c_common(PassDesc &d, const pf_plan *p, const FftSpec &fs, size_t two
         d.lds = pf::p2d_lds_bytes(fs.n);
         return;
     }
-    if (axis >= 0 && p->mr[axis] && plain_fft && max_tc >= p->B) {
+    if (mr) {
         // compile-time mixed-radix plan: one 128-byte row of columns per tile, one tile per workgroup
         d.kind = pf::PASS_C2C_MR;
         a.tw = (const char *)p->tw_dev + p->tw_mr[axis];
@@ -1427,8 +1438,9 @@ int pf_workspace_layout(const pf_plan *p, int dir) {
 
 const char *pf_pass_kernel(const pf_plan *p, int dir, int pass) {
     if (!p || dir < 0 || dir > 1 || pass < 0 || pass >= p->npass[dir]) return "";
-    // FP64 mixed-radix passes report the runtime-radix family (pencilfft.h)
-    const bool f64 = p->pass[dir][pass].prec == PF_F64;
+    // FP64 mixed-radix passes report the runtime-radix family (pencilfft.h), but
+    // for length 256, which has a power-of-two kernel too
+    const bool f64 = p->pass[dir][pass].prec == PF_F64 && p->pass[dir][pass].a.fft.n != kMrBeforeP2;
     switch (p->pass[dir][pass].kind) {
         case pf::PASS_C2C: return "c2c_generic";
         case pf::PASS_R2C_X: return "r2c_generic";
