@@ -274,6 +274,7 @@ void set_c2c_common(PassDesc &d, const pf_plan *p, const FftSpec &fs, size_t two
     if (tuned_tc > 0 && tuned_tc < max_tc) max_tc = tuned_tc;
     d.dir = dir;
     d.prec = p->lay.precision;
+    d.nt_out = 0;
     PassArgs &a = d.a;
     std::memset(&a, 0, sizeof(a));
     a.fft = fs;
@@ -366,6 +367,17 @@ constexpr size_t kXcdRunBytes = (size_t)64 << 20;
 // -> 109, 320^3, 144 MB, 61 -> 57, FP64 600 x 400 x 450 375 -> 341; 250^3, 128 MB,
 // 29.2 -> 30.5; the forward pass 399 -> 429 at 600 x 400 x 450).
 constexpr size_t kOuterFastBytes = (size_t)128 << 20;
+
+// Mixed-radix passes that write the user's array (forward Z from lines, backward
+// X) use non-temporal stores where the workspace alone fits the 256 MB last-level
+// cache but not the arrays beside it: the next pass then still finds its rows
+// there.  Pair, cached -> non-temporal: FP32 300^3 (110 MB) 255 -> 260 us, 320^3
+// (137 MB) 304 -> 296, 360^3 (182 MB) 480 -> 443, 400^3 (254 MB) 648 -> 611, FP64
+// 300^3 (209 MB) 500 -> 475, 320 x 320 x 360 (295 MB) 733 -> 706; FP32 450^3 (358
+// MB) 992 -> 1012, 500 x 400 x 750 (586 MB) 1765 -> 1803.
+constexpr size_t kNtOutMinBytes = (size_t)128 << 20, kNtOutMaxBytes = (size_t)320 << 20;
+
+int nt_out(const pf_plan *p) { return p->w_bytes > kNtOutMinBytes && p->w_bytes <= kNtOutMaxBytes; }
 
 unsigned c2c_grid(const pf_plan *p, PassDesc &d) {
     const long long tiles = d.a.A * d.a.CB;
@@ -702,6 +714,7 @@ void build_passes(pf_plan *p) {
             x.lds = pf::mr_lds_bytes(p->nx, x.prec, 1);
             x.blocks = (unsigned)((pairs + xp - 1) / xp);
             x.a.xcd = p->w_bytes <= kXcdRunBytes;
+            x.nt_out = dir == 1 && nt_out(p);
         }
         if (p->fast_x) {  // half-length complex transform, 16 (FP64: 8) lines per tile, persistent blocks
             x.kind = dir == 0 ? pf::PASS_R2C_P2 : pf::PASS_C2R_P2;
@@ -749,6 +762,7 @@ void build_passes(pf_plan *p) {
         // kOuterFastBytes
         if (z.kind == pf::PASS_C2C_MR)
             z.a.tile_order = dir == 1 && p->lay.stride1 && p->w_bytes > kOuterFastBytes ? 1 : 0;
+        z.nt_out = dir == 0 && nt_out(p);
         z.blocks = c2c_grid(p, z);
 
         if ((dir == 1 && p->bwd_tr) || (dir == 0 && p->fwd_tr)) {
@@ -769,6 +783,7 @@ void build_passes(pf_plan *p) {
             z2.a.in_s = dir == 1 ? zi : zo;
             z2.a.out_s = dir == 1 ? zo : zi;
             z2.a.tile_order = 0;
+            z2.nt_out = dir == 0 && nt_out(p);
             z2.blocks = c2c_grid(p, z2);
             // Y: in place along the contiguous ky lines of W', 16 adjacent kx per tile
             PassDesc y2;

@@ -267,12 +267,14 @@ __device__ __forceinline__ T mr_ld1(const void *base, unsigned off) {
 // PIN (FP64 values that travelled LDS in halves): the parts pass through an empty
 // asm statement first, so that they are not held as one 4-register value from
 // the first half's arrival on (25 x 40: 260 registers spilled)
-template <typename T, bool PIN = false>
+template <typename T, bool PIN = false, bool NT = false>
 __device__ __forceinline__ void mr_st(void *base, unsigned off, cx<T> v) {
     typedef T v2 __attribute__((ext_vector_type(2)));
     if constexpr (PIN && sizeof(T) == 8) asm volatile("" : "+v"(v.x), "+v"(v.y));
     const v2 u = {v.x, v.y};
-    *(PF_GLOBAL v2 *)((PF_GLOBAL char *)base + off) = u;
+    PF_GLOBAL v2 *p = (PF_GLOBAL v2 *)((PF_GLOBAL char *)base + off);
+    if constexpr (NT) __builtin_nontemporal_store(u, p);
+    else *p = u;
 }
 // 16 bytes, aligned: two FP32 values or one FP64 value
 template <typename T>
@@ -290,9 +292,11 @@ __device__ __forceinline__ void mr_st16(void *base, unsigned off, const cx<T> (&
     for (int i = 0; i < (int)(16 / sizeof(cx<T>)); ++i) u[2 * i] = v[i].x, u[2 * i + 1] = v[i].y;
     *(PF_GLOBAL vv *)((PF_GLOBAL char *)base + off) = u;
 }
-template <typename T>
+template <typename T, bool NT>
 __device__ __forceinline__ void mr_st1(void *base, unsigned off, T v) {
-    *(PF_GLOBAL T *)((PF_GLOBAL char *)base + off) = v;
+    PF_GLOBAL T *p = (PF_GLOBAL T *)((PF_GLOBAL char *)base + off);
+    if constexpr (NT) __builtin_nontemporal_store(v, p);
+    else *p = v;
 }
 
 // ---- launch arguments --------------------------------------------------------------
@@ -303,7 +307,7 @@ __device__ __forceinline__ void mr_st1(void *base, unsigned off, T v) {
 // Strides are in elements; every one of a
 // grid up to 8192^3 fits 32 bits.
 enum : unsigned { MR_BACKWARD = 1, MR_IN_LINES = 2, MR_OUT_LINES = 4, MR_BATCH = 8, MR_IN_USER = 16, MR_OUT_USER = 32,
-                MR_XCD = 64, MR_OUTER_FAST = 128 };
+                MR_XCD = 64, MR_OUTER_FAST = 128, MR_NT_STORES = 256 };
 struct MrArgs {
     const void *in;
     void *out;
@@ -525,17 +529,24 @@ __device__ __forceinline__ void mr_c2c_body(const MrArgs &a, unsigned ta, unsign
                 }
             });
         const int tid = mr_fresh(threadIdx.x);
+        auto store = [&](auto nt) {
 #pragma unroll
-        for (int i = 0; i < ITEMS; ++i) {
-            const int f = tid + i * NT;
-            const int cc = f / N, p = f - cc * N;
-            if (f < C * N && cc < ncol) mr_st<T, S::SPLIT>(out, ((unsigned)cc * a.c.oss + p) * CS, cmk<T>(r[i].x, r[i].y * sgn));
-        }
+            for (int i = 0; i < ITEMS; ++i) {
+                const int f = tid + i * NT;
+                const int cc = f / N, p = f - cc * N;
+                if (f < C * N && cc < ncol)
+                    mr_st<T, S::SPLIT, decltype(nt)::value>(out, ((unsigned)cc * a.c.oss + p) * CS,
+                                                            cmk<T>(r[i].x, r[i].y * sgn));
+            }
+        };
+        if (a.flags & MR_NT_STORES) store(std::true_type());
+        else store(std::false_type());
     } else if (j < N1 && cv) {
         const unsigned off = ((unsigned)j * a.c.oss + c) * CS;
         const size_t step = (size_t)N1 * a.c.oss;
 #pragma unroll
-        for (int k2 = 0; k2 < N2; ++k2) mr_st<T, S::SPLIT>(out + k2 * step, off, cmk<T>(y[k2].x, y[k2].y * sgn));
+        for (int k2 = 0; k2 < N2; ++k2)
+            mr_st<T, S::SPLIT>(out + k2 * step, off, cmk<T>(y[k2].x, y[k2].y * sgn));
     }
 }
 
@@ -822,14 +833,19 @@ __device__ __forceinline__ void mr_c2r_body(const MrArgs &a, unsigned tile, unsi
         for (int n2 = 0; n2 < N2; ++n2) y[n2] = lds[(c2 * N1 + k1) * S::P2 + n2];
         DftMR<T, N2>::run(y);
         const unsigned ga = g0 + 2 * c2;
-        if (ga < lines) {
+        auto store = [&](auto nt) {
+            constexpr bool NTS = decltype(nt)::value;
+            if (ga < lines) {
 #pragma unroll
-            for (int k2 = 0; k2 < N2; ++k2) mr_st1<T>(out, (2 * c2 * N + k1 + N1 * k2) * RS, y[k2].x);
-        }
-        if (ga + 1 < lines) {
+                for (int k2 = 0; k2 < N2; ++k2) mr_st1<T, NTS>(out, (2 * c2 * N + k1 + N1 * k2) * RS, y[k2].x);
+            }
+            if (ga + 1 < lines) {
 #pragma unroll
-            for (int k2 = 0; k2 < N2; ++k2) mr_st1<T>(out, ((2 * c2 + 1) * N + k1 + N1 * k2) * RS, -y[k2].y);
-        }
+                for (int k2 = 0; k2 < N2; ++k2) mr_st1<T, NTS>(out, ((2 * c2 + 1) * N + k1 + N1 * k2) * RS, -y[k2].y);
+            }
+        };
+        if (a.flags & MR_NT_STORES) store(std::true_type());
+        else store(std::false_type());
     }
 }
 

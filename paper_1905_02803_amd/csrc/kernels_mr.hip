@@ -175,6 +175,7 @@ hipError_t mr_launch(const PassDesc &d, hipStream_t s) {
         grid = dim3(grid.y, grid.x);
         m.flags |= MR_OUTER_FAST;
     }
+    if (d.nt_out) m.flags |= MR_NT_STORES;
     const int what = what_of(d.kind);
     return mr_go(what < 0 ? nullptr : mr_kernel(d.a.fft.n, d.prec, what), grid, d.threads, d.lds, m, s);
 }

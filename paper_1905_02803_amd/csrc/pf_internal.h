@@ -135,6 +135,7 @@ struct PassDesc {
     unsigned blocks;
     unsigned threads;
     size_t lds;
+    int nt_out; // mixed-radix Z forward and X backward passes: 1 to write the user's array with non-temporal stores
     PassArgs a;
 };
 

@@ -1,5 +1,6 @@
 """Mixed-radix passes on workspaces above and below 128 MB, where the backward Z
-pass changes the order of its workgroups (ky first above), both layouts and
+pass changes the order of its workgroups (ky first above) and the passes that
+write the user arrays take non-temporal stores (up to 320 MB), both layouts and
 precisions, ragged last column blocks included, against the FP64 oracle.
 
 Bounds on the relative L2 error: 1e-6 in FP32, 1e-14 in FP64 (at most 10
@@ -26,6 +27,7 @@ def rel(a, b):
     (300, 288, 320, False),  # 112 MB
     (300, 350, 320, False),  # 137 MB
     (300, 486, 480, False),  # 285 MB
+    (300, 486, 560, False),  # 332 MB
     (200, 250, 300, True),   # 119 MB
     (210, 250, 324, True),   # 138 MB
     (150, 480, 486, True),   # 285 MB
