@@ -317,11 +317,11 @@ int pf_workspace_layout(const pf_plan *p, int dir);
  * string, "" for an invalid plan / dir / pass): "c2c_generic", "r2c_generic",
  * "c2r_generic" (radix plan read at run time, Sec. 2's 1D transforms as a
  * stage loop; in FP64 also the compile-time two-step plan of the "mixed"
- * lengths); "c2c_pow2", "r2c_pow2", "c2r_pow2" (power-of-two lengths from 512,
- * radix plan fixed at compile time, persistent workgroups; 256 too where the
- * mixed kernel does not run); "c2c_mixed",
+ * lengths); "c2c_pow2", "r2c_pow2", "c2r_pow2" (power-of-two lengths from 256,
+ * radix plan fixed at compile time, persistent workgroups, where the mixed
+ * kernel is not the faster); "c2c_mixed",
  * "r2c_mixed", "c2r_mixed" (7-smooth lengths 16 .. 1024 but 343 and 686, with
- * a compile-time two-step plan, FP32; C2C length 256 in both precisions); "xy_fused" (fused_xy); "remap", "fill", "box" (reorders of
+ * a compile-time two-step plan, FP32; C2C lengths 256 and 512 in both precisions); "xy_fused" (fused_xy); "remap", "fill", "box" (reorders of
  * the processor-grid and share-only plans).  Introspection only.
  */
 const char *pf_pass_kernel(const pf_plan *p, int dir, int pass);

@@ -266,6 +266,15 @@ int built_options(int nx, int ny, const pf_layout *l) {
 // us against 3246), and the matrix-core variants exist there only.
 constexpr int kMrBeforeP2 = 256;
 
+// Backward Z pass from Z-pencil lines on the blocked workspace: up to length 512
+// above 320 MB of workspace, where the persistent kernel reads the lines at 4
+// TB/s (768 x 512 x 512 FP32 pass 406 -> 334 us, pair 2071 -> 1984; 500 x 512 x 512
+// FP64 518 -> 414, 2646 -> 2546; 1024 x 600 x 512 FP32 544 -> 516; below, 384 x 384
+// x 512, 240 MB, 118 -> 122, 100 x 100 x 512 FP64 21 -> 24.5; length 1024 at 1024^3
+// 1866 -> 2662).  Forward, the persistent kernel is the faster (351 against 417).
+constexpr int kMrBeforeP2BwdZ = 512;
+constexpr size_t kMrBwdZBytes = (size_t)320 << 20;
+
 // The power-of-two kernel serves every side: the padded workspace (whole
 // 16-column blocks, 16-byte aligned rows), contiguous lines, and unaligned
 // rows (Side::v8).
@@ -281,7 +290,10 @@ void set_c2c_common(PassDesc &d, const pf_plan *p, const FftSpec &fs, size_t two
     a.tw = (const char *)p->tw_dev + twoff;
     a.C = p->nxh;
     const bool mr = axis >= 0 && p->mr[axis] && plain_fft && max_tc >= p->B;
-    const bool mr_first = mr && fs.n <= kMrBeforeP2 && !(p->lay.precision == PF_F64 && p->bwd_tr);
+    const bool mr_first =
+        mr && ((fs.n <= kMrBeforeP2 && !(p->lay.precision == PF_F64 && p->bwd_tr)) ||
+               (fs.n <= kMrBeforeP2BwdZ && axis == 2 && dir > 0 && p->lay.stride1 && !p->bwd_tr &&
+                p->lay.math == PF_PLAIN && p->w_bytes > kMrBwdZBytes));
     if (!mr_first && !p->opt.generic_only && pf::p2_supported(fs.n, p->lay.precision) && pf::p2_tc(fs.n) <= max_tc) {
         // compile-time radix plan, persistent blocks (grid set once the tile count is known)
         d.kind = pf::PASS_C2C_P2;
@@ -1454,8 +1466,8 @@ int pf_workspace_layout(const pf_plan *p, int dir) {
 const char *pf_pass_kernel(const pf_plan *p, int dir, int pass) {
     if (!p || dir < 0 || dir > 1 || pass < 0 || pass >= p->npass[dir]) return "";
     // FP64 mixed-radix passes report the runtime-radix family (pencilfft.h), but
-    // for length 256, which has a power-of-two kernel too
-    const bool f64 = p->pass[dir][pass].prec == PF_F64 && p->pass[dir][pass].a.fft.n != kMrBeforeP2;
+    // for the C2C lengths that have a power-of-two kernel too
+    const bool f64 = p->pass[dir][pass].prec == PF_F64;
     switch (p->pass[dir][pass].kind) {
         case pf::PASS_C2C: return "c2c_generic";
         case pf::PASS_R2C_X: return "r2c_generic";
@@ -1463,7 +1475,7 @@ const char *pf_pass_kernel(const pf_plan *p, int dir, int pass) {
         case pf::PASS_C2C_P2: return "c2c_pow2";
         case pf::PASS_R2C_P2: return "r2c_pow2";
         case pf::PASS_C2R_P2: return "c2r_pow2";
-        case pf::PASS_C2C_MR: return f64 ? "c2c_generic" : "c2c_mixed";
+        case pf::PASS_C2C_MR: return f64 && !pf::p2d_supported(p->pass[dir][pass].a.fft.n) ? "c2c_generic" : "c2c_mixed";
         case pf::PASS_R2C_MR: return f64 ? "r2c_generic" : "r2c_mixed";
         case pf::PASS_C2R_MR: return f64 ? "c2r_generic" : "c2r_mixed";
         case pf::PASS_FUSED_XY: return "xy_fused";

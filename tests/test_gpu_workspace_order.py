@@ -28,6 +28,8 @@ def rel(a, b):
     (300, 350, 320, False),  # 137 MB
     (300, 486, 480, False),  # 285 MB
     (300, 486, 560, False),  # 332 MB
+    (600, 288, 512, False),  # 342 MB: backward Z of length 512 on this kernel
+    (600, 144, 512, True),   # 342 MB, likewise
     (200, 250, 300, True),   # 119 MB
     (210, 250, 324, True),   # 138 MB
     (150, 480, 486, True),   # 285 MB
@@ -39,6 +41,9 @@ def test_against_oracle(nx, ny, nz, f64, stride1):
     V = synth.complex_half(ny + stride1, (nz, ny, nx // 2 + 1)).astype(np.complex128 if f64 else np.complex64)
     to_layout = oracle.to_stride1 if stride1 else (lambda a: a)
     with pf.Plan(nx, ny, nz, pf.Layout(stride1=stride1, precision=pf.PF_F64 if f64 else pf.PF_F32)) as plan:
+        if nz == 512:
+            assert plan.pass_kernel(pf.PF_DIR_BACKWARD, 0) == ("c2c_mixed" if stride1 else "c2c_pow2")
+            assert plan.pass_kernel(pf.PF_DIR_FORWARD, 2) == "c2c_pow2"
         U = plan.ftran(torch.from_numpy(u).cuda())
         b = plan.btran(torch.from_numpy(np.ascontiguousarray(to_layout(V))).cuda())
         torch.cuda.synchronize()
