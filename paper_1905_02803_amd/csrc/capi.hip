@@ -260,18 +260,21 @@ int built_options(int nx, int ny, const pf_layout *l) {
 // C2C passes up to this length take the mixed-radix kernel where the power-of-two
 // family has one too: 37 KB of LDS (FP32) and one tile per workgroup, so more of
 // them at once; 256^3 FP32 pass 26.6 us against 31.5 (pair 152 against 163), FP64
-// pair 313 against 337, 300 x 256 x 256 natural order 179 against 208.  FP64 on the
-// transposed workspace keeps the persistent kernel (512 x 256 x 256 603 us against
-// 608).  At 512 and 1024 the persistent kernel is the faster (600 x 1024 x 512 3069
-// us against 3246), and the matrix-core variants exist there only.
+// pair 313 against 337, 300 x 256 x 256 natural order 179 against 208.  FP64 with a
+// power-of-two X pass keeps the persistent kernel: on the transposed workspace it
+// is the faster (512 x 256 x 256 603 us against 608), and plans of the same
+// transform without that workspace (blocks, batches) have to give the same bits.
+// At 512 and 1024 the persistent kernel is the faster (600 x 1024 x 512 3069 us
+// against 3246), and the matrix-core variants exist there only.
 constexpr int kMrBeforeP2 = 256;
 
-// Backward Z pass from Z-pencil lines on the blocked workspace: up to length 512
-// above 320 MB of workspace, where the persistent kernel reads the lines at 4
-// TB/s (768 x 512 x 512 FP32 pass 406 -> 334 us, pair 2071 -> 1984; 500 x 512 x 512
-// FP64 518 -> 414, 2646 -> 2546; 1024 x 600 x 512 FP32 544 -> 516; below, 384 x 384
-// x 512, 240 MB, 118 -> 122, 100 x 100 x 512 FP64 21 -> 24.5; length 1024 at 1024^3
-// 1866 -> 2662).  Forward, the persistent kernel is the faster (351 against 417).
+// Backward Z pass from Z-pencil lines, X pass not a power of two (so never on the
+// transposed workspace): up to length 512 above 320 MB of workspace, where the
+// persistent kernel reads the lines at 4 TB/s (768 x 512 x 512 FP32 pass 406 -> 334
+// us, pair 2071 -> 1984; 500 x 512 x 512 FP64 518 -> 414, 2646 -> 2546; below, 384 x
+// 384 x 512, 240 MB, 118 -> 122, 100 x 100 x 512 FP64 21 -> 24.5; length 1024 at
+// 1024^3 1866 -> 2662).  Forward, the persistent kernel is the faster (351 against
+// 417).
 constexpr int kMrBeforeP2BwdZ = 512;
 constexpr size_t kMrBwdZBytes = (size_t)320 << 20;
 
@@ -291,8 +294,8 @@ void set_c2c_common(PassDesc &d, const pf_plan *p, const FftSpec &fs, size_t two
     a.C = p->nxh;
     const bool mr = axis >= 0 && p->mr[axis] && plain_fft && max_tc >= p->B;
     const bool mr_first =
-        mr && ((fs.n <= kMrBeforeP2 && !(p->lay.precision == PF_F64 && p->bwd_tr)) ||
-               (fs.n <= kMrBeforeP2BwdZ && axis == 2 && dir > 0 && p->lay.stride1 && !p->bwd_tr &&
+        mr && ((fs.n <= kMrBeforeP2 && !(p->lay.precision == PF_F64 && p->fast_x)) ||
+               (fs.n <= kMrBeforeP2BwdZ && axis == 2 && dir > 0 && p->lay.stride1 && !p->fast_x &&
                 p->lay.math == PF_PLAIN && p->w_bytes > kMrBwdZBytes));
     if (!mr_first && !p->opt.generic_only && pf::p2_supported(fs.n, p->lay.precision) && pf::p2_tc(fs.n) <= max_tc) {
         // compile-time radix plan, persistent blocks (grid set once the tile count is known)

@@ -18,10 +18,10 @@
 //
 // Bound by the HBM traffic of the pass; measured against the runtime-radix
 // kernels, which staged the tile in LDS and read their twiddles per radix stage
-// (ms per R2C + C2R pair): FP64 300 x 280 x 250 0.675 -> 0.392 (Y pass 2.55 ->
-// 6.0 TB/s), FP64 600 x 400 x 450 3.95 -> 2.28, FP32 768 x 768 x 384 3.27 ->
-// 2.45, FP32 384^3 in natural order 0.897 -> 0.672, FP32 36 x 20 x 24 0.049 ->
-// 0.026 (8.2 against 4.4 us per pass).
+// (ms per R2C + C2R pair): FP64 300 x 280 x 250 0.675 -> 0.360 (Y pass 2.55 ->
+// 6.1 TB/s), FP64 600 x 400 x 450 3.95 -> 2.20, FP32 768 x 768 x 384 3.27 ->
+// 2.41, FP32 384^3 in natural order 0.897 -> 0.618, FP32 36 x 20 x 24 0.049 ->
+// 0.020 (8.2 against 2.9 us per pass on the device).
 //
 // Long lengths exchange the real and the imaginary parts one after the other
 // through half the LDS (MrShape::SPLIT), so that several workgroups still fit

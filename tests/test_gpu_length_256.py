@@ -1,5 +1,5 @@
 """C2C passes of length 256, which take the mixed-radix kernel before the
-power-of-two one (FP64 on the transposed workspace keeps the latter): on the
+power-of-two one (FP64 with a power-of-two X pass keeps the latter): on the
 transposed workspace, on blocks and ragged natural-order rows, against the FP64
 oracle.
 
@@ -41,3 +41,31 @@ def test_against_oracle(nx, ny, nz, stride1, f64):
         torch.cuda.synchronize()
     assert rel(U.cpu().numpy(), to_layout(oracle.r2c3d(u))) < tol
     assert rel(b.cpu().numpy(), oracle.c2r3d(V, nx)) < tol
+
+
+@pytest.mark.parametrize("f64", [False, True], ids=["f32", "f64"])
+@pytest.mark.parametrize("nx,ny,nz", [(512, 256, 16), (512, 32, 256), (640, 256, 20), (600, 288, 512), (512, 320, 512)])
+def test_processor_grid_blocks_are_the_same_bits(nx, ny, nz, f64):
+    """The kernels of the m1 x m2 block layout, which never has the transposed
+    workspace, are those of the 1 x 1 plan."""
+    print(f"case length 256 blocks {nx}x{ny}x{nz} f64={f64}", flush=True)
+    cdt, rdt, prec = (np.complex128, np.float64, pf.PF_F64) if f64 else (np.complex64, np.float32, pf.PF_F32)
+    from tests.test_gpu_grid import blocks, unblocks
+
+    nxh = nx // 2 + 1
+    u = synth.uniform(nx + 7, (nz, ny, nx)).astype(rdt)
+    with pf.Plan(nx, ny, nz, pf.Layout(precision=prec)) as full:
+        U = full.ftran(torch.from_numpy(u).cuda())
+        b = full.btran(U).cpu().numpy()  # [z][y][x]
+        U = U.cpu().numpy()  # [kx][ky][kz]
+    lay = pf.Layout(m1=2, m2=3, precision=prec)
+    with pf.Plan(nx, ny, nz, lay) as grid:
+        ub = torch.from_numpy(blocks(u.transpose(2, 1, 0), nx, ny, nz, lay, pf.PF_PENCIL_X)).cuda()
+        out = torch.empty(nxh * ny * nz, dtype=getattr(torch, np.dtype(cdt).name), device="cuda")
+        back = torch.empty_like(ub)
+        pf.pf_ftran_r2c(grid.handle, ub.data_ptr(), out.data_ptr(), 0)
+        pf.pf_btran_c2r(grid.handle, out.data_ptr(), back.data_ptr(), 0)
+        torch.cuda.synchronize()
+    assert np.array_equal(unblocks(out.cpu().numpy(), (nxh, ny, nz), nx, ny, nz, lay, pf.PF_PENCIL_Z), U)
+    got = unblocks(back.cpu().numpy(), (nx, ny, nz), nx, ny, nz, lay, pf.PF_PENCIL_X)
+    assert np.array_equal(got, b.transpose(2, 1, 0))
