@@ -172,10 +172,10 @@ def summarize_trace(trace_csv: str, command: str, steps: int, warmup: int) -> No
             "(synth.batch_sizes(4, 64), 7-smooth sizes in [48, 320]^3)", *head,
             f"modes serial, serial + hipGraph, serial on 4 streams, fused, fused + hipGraph, fused on 4 "
             f"streams, with default and tuned plans: {pairs} pairs each;",
-            "k_mr_c2c<N1, N2, DIR> / k_mr_x<N1, N2, FWD>: the compile-time mixed-radix passes (length N1 N2; "
+            "k_mr_c2c<N1, N2, T> / k_mr_x<N1, N2, FWD, T>: the compile-time mixed-radix passes (length N1 N2; "
             "one launch per transform and pass in",
-            "the serial modes, per pass and length in the fused ones); k_*_b: fused launches of the runtime-radix "
-            "passes (one per pass and block size),",
+            "the serial modes; fused: k_mr_c2c_class / k_mr_x_class, one launch per pass and class of lengths); "
+            "k_*_b: fused launches of the runtime-radix passes (one per pass and block size),",
             "k_c2c_tile / k_r2c_x / k_c2r_x their serial launches", *table(rows[b0:s0])],
         "kernels_cheb_spectral_512x512x257.txt": [
             "rocprofv3 kernel-trace statistics, Chebyshev spectral step on 512 x 512 x 257 FP32 "
