@@ -324,8 +324,8 @@ void set_c2c_common(PassDesc &d, const pf_plan *p, const FftSpec &fs, size_t two
         a.tw = (const char *)p->tw_dev + p->tw_mr[axis];
         a.tc_log2 = p->b_log2;
         a.wpc_log2 = 0;
-        d.threads = (unsigned)pf::mr_threads_of(fs.n, d.prec, 0);
-        d.lds = pf::mr_lds_bytes(fs.n, d.prec, 0);
+        d.threads = (unsigned)pf::mr_threads_of(fs.n, d.prec, pf::MR_FORM_C2C);
+        d.lds = pf::mr_lds_bytes(fs.n, d.prec, pf::MR_FORM_C2C);
         return;
     }
     d.kind = pf::PASS_C2C;
@@ -725,8 +725,8 @@ void build_passes(pf_plan *p) {
             x.a.tw = (const char *)p->tw_dev + p->tw_mr[0];
             x.a.tc_log2 = ilog2(xp);
             x.a.wpc_log2 = 0;
-            x.threads = (unsigned)pf::mr_threads_of(p->nx, x.prec, 1);
-            x.lds = pf::mr_lds_bytes(p->nx, x.prec, 1);
+            x.threads = (unsigned)pf::mr_threads_of(p->nx, x.prec, pf::MR_FORM_X);
+            x.lds = pf::mr_lds_bytes(p->nx, x.prec, pf::MR_FORM_X);
             x.blocks = (unsigned)((pairs + xp - 1) / xp);
             x.a.xcd = p->w_bytes <= kXcdRunBytes;
             x.nt_out = dir == 1 && nt_out(p);
@@ -1116,14 +1116,14 @@ void add_roots(int n, std::vector<unsigned char> &host) {
 
 // The mixed-radix kernels address one tile by 32-bit byte offsets from its base:
 // whether every tile of axis i stays below 4 GB.  X: the lines of a tile lie in
-// at most 31 / ny + 2 planes of the workspace; Z: a step reaches over N2 planes (of
-// the workspace or of [nz][ny][nxh], which is no larger), or over 16 lines ny nz
-// apart; Y tiles lie in one plane, and need only that to be below 4 GB.
+// at most 31 / ny + 2 planes of the workspace; Z: an offset reaches over mr_span()
+// planes (of the workspace or of [nz][ny][nxh], which is no larger), or over 16 lines
+// ny nz apart; Y tiles lie in one plane, and need only that to be below 4 GB.
 bool mr_fits(const pf_plan *p, int i) {
     const unsigned long long lim = 1ULL << 32, plane = (unsigned long long)p->zrows * 128;
     if (i == 0) return (31 / p->ny + 2) * plane < lim;
     if (i == 1) return plane < lim;
-    return pf::mr_long_factor(p->nz) * plane < lim && 16ULL * p->ny * p->nz * p->csize < lim;
+    return pf::mr_span(p->nz, p->lay.precision) * plane < lim && 16ULL * p->ny * p->nz * p->csize < lim;
 }
 
 }  // namespace
@@ -1269,8 +1269,8 @@ static int plan_create(int nx, int ny, int nz, const pf_layout *l, const PlanOpt
         if (e == hipSuccess && l->precision == PF_F64 && !o.generic_only && pf::p2d_supported(n)) e = pf::p2d_prepare(n);
     }
     for (int i = 0; i < 3; ++i)
-        if (e == hipSuccess && p->mr[i]) e = pf::mr_prepare(axis_n[i], l->precision, i == 0);
-    if (e == hipSuccess && p->spec_mr) e = pf::mr_prepare(p->fz.n, l->precision, 0);
+        if (e == hipSuccess && p->mr[i]) e = pf::mr_prepare(axis_n[i], l->precision, i == 0 ? pf::MR_FORM_X : pf::MR_FORM_C2C);
+    if (e == hipSuccess && p->spec_mr) e = pf::mr_prepare(p->fz.n, l->precision, pf::MR_FORM_SPEC);
     const bool cheb_p2 = l->third == PF_THIRD_CHEB && !o.generic_only && pf::p2_supported(p->fz.n, l->precision);
     if (e == hipSuccess && cheb_p2) e = pf::p2_spec_prepare(p->fz.n);
     if (e == hipSuccess && p->fast_x) e = pf::p2x_prepare(nx, l->precision);

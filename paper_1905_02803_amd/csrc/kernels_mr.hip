@@ -26,7 +26,7 @@ namespace {
 
 template <typename T, int... C>
 unsigned class_threads(int cls, bool x, std::integer_sequence<int, C...>) {
-    static constexpr int c2c[] = {mr_class_c2c_threads<T>(C)...}, xs[] = {mr_class_x_threads<T>(C)...};
+    static constexpr int c2c[] = {mr_class_c2c_threads<T>(C)...}, xs[] = {mr_class_x_threads<T, C>()...};
     return (unsigned)(x ? xs[cls] : c2c[cls]);
 }
 
@@ -39,15 +39,17 @@ const void *class_kernel(int cls, int prec, int what) {
     return (prec ? f64 : f32)[cls](what);
 }
 
-struct MrSizes {  // launch shape of one length in one precision
-    int c2c_threads, x_threads, x_pairs;
-    size_t c2c_lds, x_lds;
+struct MrSizes {  // launch shapes of one length in one precision: C2C, X, spectral step
+    int threads[3], x_pairs, span;
+    size_t lds[3];
 };
 
 template <typename T, int I>
 constexpr MrSizes sizes_at() {  // the kernels' own tile constants, so that host and device sizes agree
-    using S = MrShape<T, kMrLen[I].n1, kMrLen[I].n2>;
-    return MrSizes{S::CTHREADS, S::XTHREADS, S::XP, (size_t)S::CLDS, (size_t)S::XLDS};
+    using S = MrShape<T, MrPlan<T, I>>;
+    using Z = MrShape<T, MrTwoStep<T, kMrLen[I].n1, kMrLen[I].n2>>;
+    return MrSizes{{S::CTHREADS, S::XTHREADS, Z::CTHREADS}, S::XP, S::SPAN,
+                   {(size_t)S::CLDS, (size_t)S::XLDS, (size_t)Z::CLDS}};
 }
 template <typename T, int... I>
 const MrSizes &sizes_of(int index, std::integer_sequence<int, I...>) {
@@ -118,14 +120,14 @@ MrArgs pack(int kind, int dir, int prec, const PassArgs &a) {
 
 bool mr_supported(int n, int prec) { return (prec == 0 || prec == 1) && mr_index(n) >= 0; }
 
-int mr_threads_of(int n, int prec, int xpass) {
+int mr_threads_of(int n, int prec, int form) {
     const int i = mr_index(n);
-    return i < 0 ? 0 : xpass ? sizes(i, prec).x_threads : sizes(i, prec).c2c_threads;
+    return i < 0 ? 0 : sizes(i, prec).threads[form];
 }
 
-int mr_long_factor(int n) {
+int mr_span(int n, int prec) {
     const int i = mr_index(n);
-    return i < 0 ? 0 : kMrLen[i].n2;
+    return i < 0 ? 0 : sizes(i, prec).span;
 }
 
 int mr_x_pairs(int n, int prec) {
@@ -133,23 +135,22 @@ int mr_x_pairs(int n, int prec) {
     return i < 0 ? 0 : sizes(i, prec).x_pairs;
 }
 
-size_t mr_lds_bytes(int n, int prec, int xpass) {
+size_t mr_lds_bytes(int n, int prec, int form) {
     const int i = mr_index(n);
-    return i < 0 ? 0 : xpass ? sizes(i, prec).x_lds : sizes(i, prec).c2c_lds;
+    return i < 0 ? 0 : sizes(i, prec).lds[form];
 }
 
-hipError_t mr_prepare(int n, int prec, int xpass) {
-    const size_t lds = mr_lds_bytes(n, prec, xpass);
+hipError_t mr_prepare(int n, int prec, int form) {
+    const size_t lds = mr_lds_bytes(n, prec, form);
     if (lds <= 64 * 1024) return hipSuccess;  // the default limit
-    hipError_t e = hipSuccess;
     for (int what : {MR_C2C, MR_R2C, MR_C2R, MR_SPEC}) {
-        const bool x = what == MR_R2C || what == MR_C2R;
-        if (x != (xpass != 0) || e != hipSuccess) continue;
+        if (form != (what == MR_C2C ? MR_FORM_C2C : what == MR_SPEC ? MR_FORM_SPEC : MR_FORM_X)) continue;
         const void *k = mr_kernel(n, prec, what);
-        if (!k && what == MR_SPEC) continue;  // odd lengths have none
-        e = k ? hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) : hipErrorInvalidValue;
+        if (!k) return hipErrorInvalidValue;
+        const hipError_t e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+        if (e != hipSuccess) return e;
     }
-    return e;
+    return hipSuccess;
 }
 
 int mr_batch_class(int n) {
@@ -190,8 +191,8 @@ hipError_t mr_spec_launch(const PassArgs &a, int prec, int adj, int nx, hipStrea
     m.s.sa = (unsigned)a.in_s.sa, m.s.sb = (unsigned)a.in_s.sblk, m.s.ss = (unsigned)a.in_s.sp;
     m.s.nx = (unsigned)nx, m.s.ny = (unsigned)a.A;
     m.flags = adj ? MR_BACKWARD : 0u;
-    return mr_go(mr_kernel(n, prec, MR_SPEC), dim3((unsigned)a.CB, (unsigned)a.A), (unsigned)mr_threads_of(n, prec, 0),
-                 mr_lds_bytes(n, prec, 0), m, s);
+    return mr_go(mr_kernel(n, prec, MR_SPEC), dim3((unsigned)a.CB, (unsigned)a.A), (unsigned)mr_threads_of(n, prec, MR_FORM_SPEC),
+                 mr_lds_bytes(n, prec, MR_FORM_SPEC), m, s);
 }
 
 hipError_t mr_launch_batch(const BatchLaunch &L, hipStream_t s) {

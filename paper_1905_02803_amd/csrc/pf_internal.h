@@ -219,11 +219,12 @@ hipError_t p2_fused_launch(const FusedArgs &f, int fwd, int nx, int ny, unsigned
 // length n the table holds; one tile per workgroup.  a.tw: W_n^m, m < n
 // (forward sign).
 bool mr_supported(int n, int prec);
-int mr_long_factor(int n);                      // N2 of n = N1 N2 (0: not in the table)
-int mr_threads_of(int n, int prec, int xpass);  // threads per workgroup of the C2C (xpass 0) or X kernel
-int mr_x_pairs(int n, int prec);                // line pairs per X tile (a power of two)
-size_t mr_lds_bytes(int n, int prec, int xpass);
-hipError_t mr_prepare(int n, int prec, int xpass);  // allow the kernels their dynamic LDS
+enum MrForm { MR_FORM_C2C = 0, MR_FORM_X = 1, MR_FORM_SPEC = 2 };
+int mr_span(int n, int prec);                  // points of a column that one 32-bit offset reaches over (0: not in the table)
+int mr_threads_of(int n, int prec, int form);  // threads per workgroup of the C2C, X or spectral-step kernel
+int mr_x_pairs(int n, int prec);               // line pairs per X tile (a power of two)
+size_t mr_lds_bytes(int n, int prec, int form);
+hipError_t mr_prepare(int n, int prec, int form);  // allow the kernels their dynamic LDS
 hipError_t mr_launch(const PassDesc &d, hipStream_t s);
 // Class of lengths whose transforms share a batched launch (BatchLaunch.cls), -1: a launch per length.
 int mr_batch_class(int n);
