@@ -881,8 +881,8 @@ __device__ __forceinline__ void mr_c2c_body(const MrArgs &a, unsigned ta, unsign
 // multiply them on store (they act along z alone, so they commute with X and
 // Y).  The second DFT takes its factors in the other order, so that its step 1
 // (N2 points, k1 + N1 k2) finds its inputs in the registers where the first one's
-// step 2 left them: two trips through LDS for both.  The multiplier is computed
-// in FP64 for either precision.
+// step 2 left them: two trips through LDS for both.  The multiplier and the product
+// with it are computed in FP64 for either precision and rounded once.
 // Replaces a chain of Z pass, product, Z pass (and two weight passes of the
 // adjoint), each over the whole array: the step and its adjoint at 320 x 300 x
 // 181 took 765 us in FP32 and 1804 us in FP64, now 365 and 622; 24 x 70 x 71,
@@ -950,12 +950,13 @@ __device__ __forceinline__ void mr_spec_body(const MrArgs &a, unsigned ta, unsig
             double r;
             if constexpr (sizeof(T) == 8) {
                 r = num / d;
-            } else {  // rounded to FP32 below: the hardware reciprocal and one Newton step suffice
+            } else {  // the hardware reciprocal (error e, 2^-23) times 1 + e + e^2
                 r = __builtin_amdgcn_rcp(d);
-                r = num * __builtin_fma(__builtin_fma(-d, r, 1.0), r, r);
+                const double e = __builtin_fma(-d, r, 1.0);
+                r = num * __builtin_fma(__builtin_fma(e, e, e), r, r);
             }
-            const T mu = (T)(d > 0.0 ? r : 0.0);
-            y[k2] = cmk<T>(-mu * y[k2].y, mu * y[k2].x);
+            const double mu = d > 0.0 ? r : 0.0;
+            y[k2] = cmk<T>((T)(-mu * (double)y[k2].y), (T)(mu * (double)y[k2].x));
         }
         DftMR<T, N2, MR_S2>::run(y);
 #pragma unroll
