@@ -128,26 +128,25 @@ struct MrSplit {
     static constexpr int B = N / A;
 };
 
-// ---- FP32 rounding ---------------------------------------------------------------
+// ---- rounding --------------------------------------------------------------------
 // A complex product is two multiply-adds per part, each of which rounds one of
 // its two products by itself.  Left to the compiler, which one depends on the
 // code around it, and so on every later change of a kernel.  On a large grid that
 // is visible: a few energetic modes (amplitude 1 over noise of 0.2 at 768 x 768 x
 // 384) leak their lines' rounding into the weak modes of the same lines at 1e-3
 // of the noise, the same amount for any choice but never the same error.  So the
-// choice is written out, and FP32 results stay what they were bit for bit.
-//
+// choice is written out: FP32 results stay what they were bit for bit, and a batch
+// gives the same bits fused and serial in either precision.
+__device__ __forceinline__ float mr_fma(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
+__device__ __forceinline__ double mr_fma(double a, double b, double c) { return __builtin_fma(a, b, c); }
+
 // a w, w read from a table (a of FIRST: the imaginary part rounds a.y w.x)
 template <typename T, bool FIRST>
 __device__ __forceinline__ cx<T> mr_cmul(cx<T> a, cx<T> w) {
-    if constexpr (sizeof(T) == 8) {
-        return cmul(a, w);
-    } else {
-        cx<T> r;
-        r.x = __builtin_fmaf(a.x, w.x, -(a.y * w.y));
-        r.y = FIRST ? __builtin_fmaf(a.x, w.y, a.y * w.x) : __builtin_fmaf(a.y, w.x, a.x * w.y);
-        return r;
-    }
+    cx<T> r;
+    r.x = mr_fma(a.x, w.x, -(a.y * w.y));
+    r.y = FIRST ? mr_fma(a.x, w.y, a.y * w.x) : mr_fma(a.y, w.x, a.x * w.y);
+    return r;
 }
 
 // Where an in-register DFT of the two-step plans stands: step 1 of the X and of
@@ -170,14 +169,10 @@ constexpr int mr_rounds(int N, int A, int where, int n2, int k1) {
 
 template <typename T, int ROUNDS>
 __device__ __forceinline__ cx<T> mr_rot(cx<T> a, T c, T s) {
-    if constexpr (sizeof(T) == 8) {
-        return crot<-1>(a, c, s);
-    } else {
-        cx<T> r;
-        r.x = (ROUNDS & 1) ? __builtin_fmaf(a.y, s, a.x * c) : __builtin_fmaf(a.x, c, a.y * s);
-        r.y = (ROUNDS & 2) ? __builtin_fmaf(a.x, -s, a.y * c) : __builtin_fmaf(a.y, c, -(a.x * s));
-        return r;
-    }
+    cx<T> r;
+    r.x = (ROUNDS & 1) ? mr_fma(a.y, s, a.x * c) : mr_fma(a.x, c, a.y * s);
+    r.y = (ROUNDS & 2) ? mr_fma(a.x, -s, a.y * c) : mr_fma(a.y, c, -(a.x * s));
+    return r;
 }
 
 // v sgn, sgn = +-1.  FP32: hidden from the compiler, which would otherwise fold the
