@@ -559,7 +559,7 @@ def other_grid_timings(pf, args, dev, stream):
             for i in range(plan.num_passes(d)):
                 tot, cnt = plan.get_timing(d, i)
                 pms = tot / max(cnt, 1)
-                passes.append({"pass": plan.pass_name(d, i), "kernel": plan.pass_kernel(d, i), "avg_ms": pms,
+                passes.append({"pass": plan.pass_name(d, i), "kernel": plan.pass_symbol(d, i), "avg_ms": pms,
                                "alg_GBps": plan.pass_bytes(d, i) / (pms * 1e-3) / 1e9})
         plan.set_timing(False)
         rec["passes"] = passes

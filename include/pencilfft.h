@@ -313,18 +313,29 @@ const char *pf_pass_name(const pf_plan *p, int dir, int pass);
 int pf_workspace_layout(const pf_plan *p, int dir);
 
 /*
- * Kernel family that runs pass `pass` of direction `dir` (a short static
- * string, "" for an invalid plan / dir / pass): "c2c_generic", "r2c_generic",
- * "c2r_generic" (radix plan read at run time, Sec. 2's 1D transforms as a
- * stage loop; in FP64 also the compile-time two-step plan of the "mixed"
- * lengths); "c2c_pow2", "r2c_pow2", "c2r_pow2" (power-of-two lengths from 256,
- * radix plan fixed at compile time, persistent workgroups, where the mixed
- * kernel is not the faster); "c2c_mixed",
- * "r2c_mixed", "c2r_mixed" (7-smooth lengths 16 .. 1024 but 343 and 686, with
- * a compile-time two-step plan, FP32; C2C lengths 256 and 512 in both precisions); "xy_fused" (fused_xy); "remap", "fill", "box" (reorders of
- * the processor-grid and share-only plans).  Introspection only.
+ * Family of pass `pass` of direction `dir` (a short static string, "" for an
+ * invalid plan / dir / pass): "c2c_generic", "r2c_generic", "c2r_generic"
+ * (radix plan read at run time, Sec. 2's 1D transforms as a stage loop);
+ * "c2c_pow2", "r2c_pow2", "c2r_pow2" (power-of-two lengths from 256, radix
+ * plan fixed at compile time, persistent workgroups, where the mixed kernel is
+ * not the faster); "c2c_mixed", "r2c_mixed", "c2r_mixed" (7-smooth lengths 16
+ * .. 1024 but 343 and 686, plan of two or three steps fixed at compile time);
+ * "xy_fused" (fused_xy); "remap", "fill", "box" (reorders of the
+ * processor-grid and share-only plans).  In FP64 the mixed passes keep the
+ * "generic" name under which callers know them (C2C lengths 256 and 512
+ * aside): pf_pass_symbol tells them apart.  Introspection only.
  */
 const char *pf_pass_kernel(const pf_plan *p, int dir, int pass);
+
+/*
+ * The kernel function that runs pass `pass` of direction `dir`, as a profiler
+ * shows it, without template arguments ("" for an invalid plan / dir / pass):
+ * "k_c2c_tile", "k_r2c_x", "k_c2r_x" (runtime-radix), "k_mr_c2c", "k_mr_x"
+ * (compile-time mixed-radix), "k_c2c_p2", "k_r2c_p2", "k_c2r_p2" and in FP64
+ * "k_c2c_p2d", "k_r2c_p2d", "k_c2r_p2d" (power-of-two), "k_xy_fused", "k_remap",
+ * "k_fill", "k_box".  Introspection only.
+ */
+const char *pf_pass_symbol(const pf_plan *p, int dir, int pass);
 
 /*
  * Algorithmic HBM bytes of one pass: every element read once and written once

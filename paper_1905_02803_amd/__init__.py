@@ -47,7 +47,7 @@ EXPORTED = (
     "pf_run_pass", "pf_pass_name", "pf_pass_bytes", "pf_set_timing", "pf_get_timing", "pf_copy",
     "pf_batch_setup", "pf_batch_offset", "pf_batch_bytes", "pf_batch_set_mode", "pf_batch_ftran_r2c",
     "pf_batch_btran_c2r", "pf_batch_destroy", "pf_spectral_step", "pf_exec_noalloc", "pf_check_status",
-    "pf_probe", "pf_pass_kernel", "pf_workspace_layout",
+    "pf_probe", "pf_pass_kernel", "pf_pass_symbol", "pf_workspace_layout",
 )
 
 
@@ -120,6 +120,7 @@ def lib():
             "pf_run_pass": (i, [vp, i, i, vp, vp, vp]),
             "pf_pass_name": (ctypes.c_char_p, [vp, i, i]),
             "pf_pass_kernel": (ctypes.c_char_p, [vp, i, i]),
+            "pf_pass_symbol": (ctypes.c_char_p, [vp, i, i]),
             "pf_workspace_layout": (i, [vp, i]),
             "pf_pass_bytes": (ctypes.c_double, [vp, i, i]),
             "pf_set_timing": (i, [vp, i]),
@@ -232,6 +233,10 @@ def pf_pass_name(h, direction: int, pass_index: int) -> str:
 
 def pf_pass_kernel(h, direction: int, pass_index: int) -> str:
     return lib().pf_pass_kernel(h, direction, pass_index).decode()
+
+
+def pf_pass_symbol(h, direction: int, pass_index: int) -> str:
+    return lib().pf_pass_symbol(h, direction, pass_index).decode()
 
 
 def pf_workspace_layout(h, direction: int) -> int:
@@ -426,6 +431,9 @@ class Plan:
 
     def pass_kernel(self, direction: int, index: int) -> str:
         return pf_pass_kernel(self.handle, direction, index)
+
+    def pass_symbol(self, direction: int, index: int) -> str:
+        return pf_pass_symbol(self.handle, direction, index)
 
     def workspace_layout(self, direction: int) -> int:
         return pf_workspace_layout(self.handle, direction)

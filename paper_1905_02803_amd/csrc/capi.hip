@@ -1468,8 +1468,9 @@ int pf_workspace_layout(const pf_plan *p, int dir) {
 
 const char *pf_pass_kernel(const pf_plan *p, int dir, int pass) {
     if (!p || dir < 0 || dir > 1 || pass < 0 || pass >= p->npass[dir]) return "";
-    // FP64 mixed-radix passes report the runtime-radix family (pencilfft.h), but
-    // for the C2C lengths that have a power-of-two kernel too
+    // FP64 mixed-radix passes keep the runtime-radix family's name (pencilfft.h;
+    // pf_pass_symbol tells them apart), but for the C2C lengths that have a
+    // power-of-two kernel too
     const bool f64 = p->pass[dir][pass].prec == PF_F64;
     switch (p->pass[dir][pass].kind) {
         case pf::PASS_C2C: return "c2c_generic";
@@ -1485,6 +1486,27 @@ const char *pf_pass_kernel(const pf_plan *p, int dir, int pass) {
         case pf::PASS_REMAP: return "remap";
         case pf::PASS_FILL: return "fill";
         case pf::PASS_BOX: return "box";
+    }
+    return "";
+}
+
+const char *pf_pass_symbol(const pf_plan *p, int dir, int pass) {
+    if (!p || dir < 0 || dir > 1 || pass < 0 || pass >= p->npass[dir]) return "";
+    const bool f64 = p->pass[dir][pass].prec == PF_F64;
+    switch (p->pass[dir][pass].kind) {
+        case pf::PASS_C2C: return "k_c2c_tile";
+        case pf::PASS_R2C_X: return "k_r2c_x";
+        case pf::PASS_C2R_X: return "k_c2r_x";
+        case pf::PASS_C2C_P2: return f64 ? "k_c2c_p2d" : "k_c2c_p2";
+        case pf::PASS_R2C_P2: return f64 ? "k_r2c_p2d" : "k_r2c_p2";
+        case pf::PASS_C2R_P2: return f64 ? "k_c2r_p2d" : "k_c2r_p2";
+        case pf::PASS_C2C_MR: return "k_mr_c2c";
+        case pf::PASS_R2C_MR:
+        case pf::PASS_C2R_MR: return "k_mr_x";
+        case pf::PASS_FUSED_XY: return "k_xy_fused";
+        case pf::PASS_REMAP: return "k_remap";
+        case pf::PASS_FILL: return "k_fill";
+        case pf::PASS_BOX: return "k_box";
     }
     return "";
 }
