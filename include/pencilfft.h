@@ -426,9 +426,10 @@ int pf_spectral_step(pf_plan *p, const void *in, void *spec, void *out, int adjo
  * persistent grids are sized per transform, are not used in a batch).  A
  * fused pass is one kernel launch per group of transforms that share a
  * kernel -- the runtime-radix passes grouped by block size, the mixed-radix
- * passes by class of lengths (16 .. 112, 120 .. 243, 245 .. 324; longer ones
- * by length) -- over the tiles of every transform of the group (a
- * device table maps each workgroup to its transform).
+ * passes by class of lengths (16 .. 112, 120 .. 243, 245 .. 324, 336 .. 512,
+ * 525 .. 720, 729 .. 1024; a length above 324 with 1024 workgroups or more by
+ * itself) -- over the tiles of every transform of the group (a device table
+ * maps each workgroup to its transform).
  *
  * pf_tune: per axis (x, y, z) a radix order (0: radix 16 first, then 8, 4, 2,
  * 3, 5, 7; 1: 8, 4, 2, 3, 5, 7; 2: 4, 2, 3, 5, 7; 3: 3, 5, 7 first, then 16,

@@ -18,7 +18,7 @@ MR_UNITS = 8
 MR_PARTS = {f"kernels_mr_{t}_{u}.hip": [f"-DPF_MR_UNIT={u}", f"-DPF_MR_UNITS={MR_UNITS}", f"-DPF_MR_T={t}",
                                         f"-DPF_MR_NAME=mr_pick_{t}_{u}"]
             for t in ("double", "float") for u in range(MR_UNITS)}
-MR_CLASSES = 3  # classes of lengths with a batched kernel (kernels_mr.h, kMrClass)
+MR_CLASSES = 6  # classes of lengths with a batched kernel (kernels_mr.h, kMrClass)
 MR_PARTS.update({f"kernels_mr_class_{t}_{c}.hip": [f"-DPF_MR_CLASS={c}", f"-DPF_MR_T={t}",
                                                    f"-DPF_MR_NAME=mr_class_{t}_{c}"]
                  for t in ("double", "float") for c in range(MR_CLASSES)})

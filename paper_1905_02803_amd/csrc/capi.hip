@@ -9,6 +9,7 @@
 #include <cstring>
 #include <mutex>
 #include <new>
+#include <tuple>
 #include <vector>
 
 #include "pencilfft.h"
@@ -1826,7 +1827,7 @@ int pf_batch_setup(int count, const int *dims, const pf_layout *l, const pf_tune
             const int in_user = k == 0, out_user = k == 2;
             // launch groups: runtime-radix passes by block size; compile-time
             // mixed-radix passes by class of lengths (one kernel per class), or by
-            // length where there is none
+            // length where a long one has workgroups enough for a launch of its own
             auto is_mr = [](pf::PassKind kd) {
                 return kd == pf::PASS_C2C_MR || kd == pf::PASS_R2C_MR || kd == pf::PASS_C2R_MR;
             };
@@ -1834,15 +1835,17 @@ int pf_batch_setup(int count, const int *dims, const pf_layout *l, const pf_tune
                 const PassDesc &d = b->plans[i]->pass[dir][k];
                 return is_mr(d.kind) ? d.a.fft.n : 0;
             };
+            std::vector<long long> of_len(8193, 0);  // workgroups of all transforms of a length
+            for (int i = 0; i < count; ++i) of_len[mr_len(i)] += b->plans[i]->pass[dir][k].blocks;
             auto mr_cls = [&](int i) {
                 const int n = mr_len(i);
-                return n ? pf::mr_batch_class(n) : -1;
+                return n ? pf::mr_batch_class(n, of_len[n]) : -1;
             };
-            auto same_group = [&](int u, int v) {
-                const PassDesc &du = b->plans[u]->pass[dir][k], &dv = b->plans[v]->pass[dir][k];
-                if (du.kind != dv.kind) return false;
-                if (mr_cls(u) >= 0 || mr_cls(v) >= 0) return mr_cls(u) == mr_cls(v);
-                return mr_len(u) == mr_len(v) && du.threads == dv.threads;
+            // (kind, class, length, threads), the last two where there is no class
+            auto group = [&](int i) {
+                const PassDesc &d = b->plans[i]->pass[dir][k];
+                const int c = mr_cls(i);
+                return std::make_tuple((int)d.kind, c < 0 ? 1 << 20 : c, c < 0 ? mr_len(i) : 0, c < 0 ? (int)d.threads : 0);
             };
             for (int i = 0; i < count; ++i) {
                 order[i] = i;
@@ -1852,11 +1855,10 @@ int pf_batch_setup(int count, const int *dims, const pf_layout *l, const pf_tune
                     return PF_EUNSUPPORTED;
                 }
             }
+            // groups of the largest lengths / blocks first, within a class the longest
             std::stable_sort(order.begin(), order.end(), [&](int u, int v) {
-                const PassDesc &du = b->plans[u]->pass[dir][k], &dv = b->plans[v]->pass[dir][k];
-                if (du.kind != dv.kind) return du.kind < dv.kind;
-                if (mr_len(u) != mr_len(v)) return mr_len(u) > mr_len(v);
-                return du.threads > dv.threads;
+                const auto gu = group(u), gv = group(v);
+                return gu != gv ? gu > gv : mr_len(u) > mr_len(v);
             });
             int f = 0;  // next free prefix slot
             for (int j = 0; j < count;) {
@@ -1877,7 +1879,7 @@ int pf_batch_setup(int count, const int *dims, const pf_layout *l, const pf_tune
                 L.b.first = Fdev + f;
                 long long blocks = 0;
                 int n = 0;
-                for (; j < count && same_group(order[j], lead); ++j, ++n) {
+                for (; j < count && group(order[j]) == group(lead); ++j, ++n) {
                     const int i = order[j];
                     const PassDesc &d = b->plans[i]->pass[dir][k];
                     A[j] = d.a;
@@ -1901,6 +1903,10 @@ int pf_batch_setup(int count, const int *dims, const pf_layout *l, const pf_tune
                 }
                 L.blocks = (unsigned)blocks;
                 L.b.count = n;
+                if (pf::mr_prepare_batch(L) != hipSuccess) {
+                    batch_free(b);
+                    return PF_EHIP;
+                }
                 b->launch[dir][k].push_back(L);
             }
         }

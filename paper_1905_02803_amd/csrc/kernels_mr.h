@@ -1274,9 +1274,11 @@ const void *mr_kernel_at(int what) {
 // length -> per class: 32 FP32 grids of 48 .. 320 points 2.04 -> 1.38 ms, 15 FP64
 // grids of 24 .. 124 points 0.357 -> 0.147 ms.
 struct MrClass {
-    int first, last, cap;  // positions; threads per column (items beyond go to a second round)
+    int first, last, cap;  // positions; threads per column (items beyond go to further rounds)
 };
-constexpr MrClass kMrClass[] = {{0, 36, 16}, {36, 60, 16}, {60, 72, 20}};  // 16 .. 112, 120 .. 243, 245 .. 324
+constexpr MrClass kMrClass[] = {{0, 36, 16},   {36, 60, 16},   {60, 72, 20},     // 16 .. 112, 120 .. 243, 245 .. 324
+                                {72, 92, 36}, {92, 107, 36}, {107, 128, 36}};  // 336 .. 512, 525 .. 720, 729 .. 1024
+constexpr int kMrLongClass = 3;  // from here on only for lengths with few workgroups (pf_batch_setup)
 constexpr int kMrClasses = (int)(sizeof(kMrClass) / sizeof(kMrClass[0]));
 
 constexpr int mr_class(int index) {

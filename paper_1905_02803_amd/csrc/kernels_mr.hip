@@ -15,8 +15,8 @@ PF_MR_EACH_UNIT(PF_MR_DECLARE, double)
 #undef PF_MR_DECLARE
 
 // the batched kernels of the classes of lengths (kernels_mr_class.hip)
-static_assert(kMrClasses == 3, "every class is named below");
-#define PF_MR_EACH_CLASS(X, T) X(T, 0) X(T, 1) X(T, 2)
+static_assert(kMrClasses == 6, "every class is named below");
+#define PF_MR_EACH_CLASS(X, T) X(T, 0) X(T, 1) X(T, 2) X(T, 3) X(T, 4) X(T, 5)
 #define PF_MR_DECLARE(T, U) const void *mr_class_##T##_##U(int what);
 PF_MR_EACH_CLASS(PF_MR_DECLARE, float)
 PF_MR_EACH_CLASS(PF_MR_DECLARE, double)
@@ -153,9 +153,24 @@ hipError_t mr_prepare(int n, int prec, int form) {
     return hipSuccess;
 }
 
-int mr_batch_class(int n) {
-    const int i = mr_index(n);
-    return i < 0 ? -1 : mr_class(i);
+// A length above 324 whose transforms have this many workgroups in all fills the chip
+// by itself and runs its own kernel (12 FP32 grids of 336 .. 480 points 9.14 ms a pair,
+// 9.87 as classes); below, a launch per length costs more than the classes' shared
+// shape (64 FP32 grids with one edge of 336 .. 1024, the others of 16 .. 32, 1.29
+// ms, 0.53 as classes, 0.84 as one launch of the runtime-radix kernels; 256 or 512
+// in place of 1024: 0.54, 0.53; 2048: the same).
+constexpr long long kMrOwnLaunch = 1024;
+
+int mr_batch_class(int n, long long blocks) {
+    const int i = mr_index(n), cls = i < 0 ? -1 : mr_class(i);
+    return cls >= kMrLongClass && blocks >= kMrOwnLaunch ? -1 : cls;
+}
+
+hipError_t mr_prepare_batch(const BatchLaunch &L) {
+    const int what = what_of(L.kind);
+    if (L.cls < 0 || what < 0 || L.lds <= 64 * 1024) return hipSuccess;
+    return hipFuncSetAttribute(class_kernel(L.cls, L.prec, what), hipFuncAttributeMaxDynamicSharedMemorySize,
+                               (int)L.lds);
 }
 
 size_t mr_entry_bytes() { return sizeof(MrArgs); }

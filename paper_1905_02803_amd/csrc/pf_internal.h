@@ -226,8 +226,10 @@ int mr_x_pairs(int n, int prec);               // line pairs per X tile (a power
 size_t mr_lds_bytes(int n, int prec, int form);
 hipError_t mr_prepare(int n, int prec, int form);  // allow the kernels their dynamic LDS
 hipError_t mr_launch(const PassDesc &d, hipStream_t s);
-// Class of lengths whose transforms share a batched launch (BatchLaunch.cls), -1: a launch per length.
-int mr_batch_class(int n);
+// Class of lengths whose transforms share a batched launch (BatchLaunch.cls), -1: a launch of its own for length n,
+// whose transforms have `blocks` workgroups in all.
+int mr_batch_class(int n, long long blocks);
+hipError_t mr_prepare_batch(const BatchLaunch &L);  // allow a class kernel its dynamic LDS
 // One transform's entry (mr_entry_bytes() bytes, smaller than PassArgs) of a batched launch's table.
 size_t mr_entry_bytes();
 void mr_entry(int kind, int dir, int prec, const PassArgs &a, void *dst);
