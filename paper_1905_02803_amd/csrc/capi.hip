@@ -260,11 +260,12 @@ int built_options(int nx, int ny, const pf_layout *l) {
 
 // C2C passes up to this length take the mixed-radix kernel where the power-of-two
 // family has one too: 37 KB of LDS (FP32) and one tile per workgroup, so more of
-// them at once; 256^3 FP32 pass 26.6 us against 31.5 (pair 152 against 163), FP64
+// them at once; 256^3 FP32 pass 26.6 us against 31.5 (pair 159 against 170), FP64
 // pair 313 against 337, 300 x 256 x 256 natural order 179 against 208.  FP64 with a
 // power-of-two X pass keeps the persistent kernel: on the transposed workspace it
-// is the faster (512 x 256 x 256 603 us against 608), and plans of the same
-// transform without that workspace (blocks, batches) have to give the same bits.
+// is the faster (512 x 256 x 256 603 us against 608), and block plans of the same
+// transform, which do not have that workspace, have to give the same bits (batches
+// do not: theirs run no power-of-two kernel, X included).
 // At 512 and 1024 the persistent kernel is the faster (600 x 1024 x 512 3069 us
 // against 3246), and the matrix-core variants exist there only.
 constexpr int kMrBeforeP2 = 256;
@@ -384,13 +385,14 @@ constexpr size_t kXcdRunBytes = (size_t)64 << 20;
 // 29.2 -> 30.5; the forward pass 399 -> 429 at 600 x 400 x 450).
 constexpr size_t kOuterFastBytes = (size_t)128 << 20;
 
-// Mixed-radix passes that write the user's array (forward Z from lines, backward
-// X) use non-temporal stores where the workspace alone fits the 256 MB last-level
-// cache but not the arrays beside it: the next pass then still finds its rows
-// there.  Pair, cached -> non-temporal: FP32 300^3 (110 MB) 255 -> 260 us, 320^3
-// (137 MB) 304 -> 296, 360^3 (182 MB) 480 -> 443, 400^3 (254 MB) 648 -> 611, FP64
-// 300^3 (209 MB) 500 -> 475, 320 x 320 x 360 (295 MB) 733 -> 706; FP32 450^3 (358
-// MB) 992 -> 1012, 500 x 400 x 750 (586 MB) 1765 -> 1803.
+// Mixed-radix passes that write the user's array (forward Z from lines but for FP64
+// tiles in halves, backward X) use non-temporal stores where the 256 MB last-level
+// cache holds the workspace, or most of it, but not the arrays beside it: the
+// next pass then still finds its rows there.  Pair, cached -> non-temporal: FP32
+// 300^3 (110 MB) 255 -> 260 us, 360^3 (190 MB) 498 -> 464, 400^3 (254 MB) 659 ->
+// 635, 405^3 (260 MB) 668 -> 649, 420^3 (301 MB) 801 -> 797; FP64 300^3 (209 MB)
+// 514 -> 486, 320^3 (263 MB) 649 -> 616, 320 x 320 x 360 (295 MB) 747 -> 719, 336^3
+// (303 MB) 754 -> 733, 350^3 (329 MB) 823 -> 829; FP32 450^3 (371 MB) 992 -> 1012.
 constexpr size_t kNtOutMinBytes = (size_t)128 << 20, kNtOutMaxBytes = (size_t)320 << 20;
 
 int nt_out(const pf_plan *p) { return p->w_bytes > kNtOutMinBytes && p->w_bytes <= kNtOutMaxBytes; }

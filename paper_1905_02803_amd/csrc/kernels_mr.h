@@ -384,7 +384,7 @@ __device__ __forceinline__ T mr_ld1(const void *base, unsigned off) {
 }
 // PIN (FP64 values that travelled LDS in halves): the parts pass through an empty
 // asm statement first, so that they are not held as one 4-register value from
-// the first half's arrival on (25 x 40: 260 registers spilled)
+// the first half's arrival on (25 x 40 points: 260 registers spilled, 9 so)
 template <typename T, bool PIN = false, bool NT = false>
 __device__ __forceinline__ void mr_st(void *base, unsigned off, cx<T> v) {
     typedef T v2 __attribute__((ext_vector_type(2)));
@@ -828,7 +828,12 @@ __device__ __forceinline__ void mr_c2c_body(const MrArgs &a, unsigned ta, unsign
                                                                 cmk<T>(r[0][i].x, mr_flip(r[0][i].y, sgn)));
                 }
             };
-            if (a.flags & MR_NT_STORES) store(std::true_type());
+            // FP64 tiles in halves have no room for two copies of the stores: with both, 960
+            // points took 79 / 85 us forward / backward in place of 65 / 63 (60 x 300 x 960)
+            // and 1000 and 1008 points spilled 14 and 2 registers in place of 9 and none, for
+            // 1% at 768 points
+            if constexpr (S::SPLIT && sizeof(T) == 8) store(std::false_type());
+            else if (a.flags & MR_NT_STORES) store(std::true_type());
             else store(std::false_type());
         } else if (cv) {
             const unsigned off = ((unsigned)j * a.c.oss + c) * CS;
