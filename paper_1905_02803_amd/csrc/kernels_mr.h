@@ -538,7 +538,8 @@ __host__ __device__ constexpr int mr_c2c_cols() {
     const int w = 64 / mr_cols<T>();
     if (P::STEPS == 2) return mr_ceil(mr_max(P::G(0), P::G(1)), w) * w;
     const int J1 = P::N / P::G(1), J2 = P::N / P::G(2);
-    return 128 * P::N > kMrSplitAbove && P::N / P::G(0) <= 48 && mr_max(J1, J2) <= 3 * 48 ? 48 : 64;
+    const bool split = 128 * P::G(0) * (P::N / P::G(0) | 1) > kMrSplitAbove;
+    return split && P::N / P::G(0) <= 48 && mr_max(J1, J2) <= 3 * 48 ? 48 : 64;
 }
 // X kernels: line pairs per tile (a power of two; the lines' workspace rows
 // are separate, so the tile width does not change the row accesses): 4, more
