@@ -417,6 +417,20 @@ __device__ __forceinline__ void mr_st1(void *base, unsigned off, T v) {
     else *p = v;
 }
 
+// f(k, tw[j k]) for 0 < k < N, the loads H ahead of their uses: where the compiler keeps
+// the order of the source, one load at a time waits out its latency N times (360 points,
+// forward X pass in FP32: 56 us on 360 x 360 x 200, 45.5 with 8 ahead).  FP64 4 ahead still
+// waits (400 points: 117 us on 400 x 256 x 288, 105 with 6).  The C2C kernels hide it: 0.
+template <typename T, int N, int H, typename F>
+__device__ __forceinline__ void mr_twiddles(const cx<T> *tw, int j, F f) {
+    cx<T> w[N];
+#pragma unroll
+    for (int k = 1; k < N + H; ++k) {
+        if (k < N) w[k] = mr_ld<T>(tw, j * k * sizeof(cx<T>));
+        if (k > H) f(k - H, w[k - H]);
+    }
+}
+
 // ---- plans ----------------------------------------------------------------------
 // What a step does with the points of one item, held in registers: step<S>(v, j,
 // tw), j the item's index among the N / G(S) items of the step.  Item j of step S
@@ -424,15 +438,16 @@ __device__ __forceinline__ void mr_st1(void *base, unsigned off, T v) {
 // steps, splits j = k + K h; output o goes to position k + K (h G(S) + o).  tw: W_N^m.
 template <typename T, int N1, int N2>
 struct MrTwoStep {
+    static constexpr bool BOUNDED = true;  // see MrShape::XWAVES
     static constexpr int N = N1 * N2, STEPS = 2;
     static constexpr int G(int s) { return s == 0 ? N1 : s == 1 ? N2 : 1; }
     template <int S, bool XPASS>
     __device__ __forceinline__ static void step(cx<T> *v, int j, const cx<T> *tw) {
         if constexpr (S == 0) {
             DftMR<T, N1, !XPASS ? MR_C1 : N == 256 ? MR_S2 : MR_X1>::run(v);
-#pragma unroll
-            for (int k1 = 1; k1 < N1; ++k1)
-                v[k1] = mr_cmul<T, (N == 16 || (XPASS && N == 256))>(v[k1], mr_ld<T>(tw, j * k1 * sizeof(cx<T>)));
+            mr_twiddles<T, N1, !XPASS ? 0 : sizeof(T) == 4 ? 8 : 6>(tw, j, [&](int k, cx<T> w) {
+                v[k] = mr_cmul<T, (N == 16 || (XPASS && N == 256))>(v[k], w);
+            });
         } else {
             DftMR<T, N2, MR_S2>::run(v);
         }
@@ -445,6 +460,7 @@ struct MrTwoStep {
 // R}^{r k}.  In step 0 these are constants, later they are read from the table.
 template <int N_>
 struct MrStaged {
+    static constexpr bool BOUNDED = false;
     static constexpr int N = N_;
     static constexpr MrStages P = mr_stages(N);
     static constexpr int STEPS = P.steps;
@@ -522,6 +538,7 @@ __host__ __device__ constexpr int mr_cols() {
     return 128 / (int)sizeof(cx<T>);
 }
 constexpr int mr_max(int a, int b) { return a > b ? a : b; }
+constexpr int mr_min(int a, int b) { return a < b ? a : b; }
 constexpr int mr_ceil(int a, int b) { return (a + b - 1) / b; }
 
 // Threads per column of the C2C kernel.  Two steps: as many as the larger step
@@ -570,6 +587,14 @@ struct MrShape {
     // pair at pitch SP (= 16 mod 32, >= N)
     static constexpr int XP = mr_xp<T, P>();
     static constexpr int XTHREADS = mr_x_threads<T, P>();
+    // Wavefronts per SIMD that the X kernels leave registers for.  Two steps in FP32: the
+    // larger step's points and 24 more; unbounded, forward 20 x 24 took 89 registers (5
+    // wavefronts) and 77 us on 480 x 360 x 250, bounded 71 .. 73.  FP64: 20 x 20 took 184 (2)
+    // and 110 us forward on 400 x 256 x 288, with 3 105; 30 x 30 264 (1) and 203 us on 900 x
+    // 300 x 200, with 2 (10 spilled) 195.  The staged plans lose by a bound (they spill up to 78).
+    static constexpr int XWAVES = sizeof(T) == 8 ? mr_max(G0, G1) <= 21 ? 3 : 2
+                                  : P::BOUNDED   ? mr_min(7, 512 / ((2 * mr_max(G0, G1) + 31) / 8 * 8))
+                                                 : 1;
     static constexpr int NXH = N / 2 + 1, NKB = (NXH + C - 1) / C;  // modes and column blocks of a line
     static constexpr int SP = N + ((16 - N % 32) % 32 + 32) % 32;
     static constexpr int XLDS = mr_max(XP * G0 * P2, XP * SP) * (int)sizeof(cx<T>);
@@ -765,12 +790,13 @@ __device__ __forceinline__ void mr_c2c_body(const MrArgs &a, unsigned ta, unsign
             });
     } else {
         const unsigned off = ((unsigned)j * a.c.iss + c) * CS;
-        mr_items<J0, CT, I0>(j, [&](int it, int) {
-            if (cv) {
+#pragma unroll
+        for (int it = 0; it < I0; ++it) {
+            if (j + it * CT < J0 && cv) {
 #pragma unroll
                 for (int m = 0; m < G0; ++m) x[it][m] = mr_ld<T>(in + (size_t)(it * CT + m * J0) * a.c.iss, off);
             }
-        });
+        }
     }
     mr_items<J0, CT, I0>(j, [&](int it, int q) {
 #pragma unroll
@@ -836,14 +862,17 @@ __device__ __forceinline__ void mr_c2c_body(const MrArgs &a, unsigned ta, unsign
             if constexpr (S::SPLIT && sizeof(T) == 8) store(std::false_type());
             else if (a.flags & MR_NT_STORES) store(std::true_type());
             else store(std::false_type());
-        } else if (cv) {
+        } else {
             const unsigned off = ((unsigned)j * a.c.oss + c) * CS;
-            mr_items<J, CT, I>(j, [&](int it, int) {
 #pragma unroll
-                for (int o = 0; o < G; ++o)
-                    mr_st<T, S::SPLIT>(out + (size_t)(it * CT + o * J) * a.c.oss, off,
-                                       cmk<T>(v[it][o].x, mr_flip(v[it][o].y, sgn)));
-            });
+            for (int it = 0; it < I; ++it) {
+                if (j + it * CT < J && cv) {
+#pragma unroll
+                    for (int o = 0; o < G; ++o)
+                        mr_st<T, S::SPLIT>(out + (size_t)(it * CT + o * J) * a.c.oss, off,
+                                           cmk<T>(v[it][o].x, mr_flip(v[it][o].y, sgn)));
+                }
+            }
         }
     };
     if constexpr (P::STEPS == 2) {
@@ -921,8 +950,7 @@ __device__ __forceinline__ void mr_spec_body(const MrArgs &a, unsigned ta, unsig
             }
         }
         DftMR<T, N1, MR_X1>::run(x);
-#pragma unroll
-        for (int k1 = 1; k1 < N1; ++k1) x[k1] = cmul(x[k1], mr_ld<T>(tw, j * k1 * CS));
+        mr_twiddles<T, N1, sizeof(T) == 4 ? 8 : 0>(tw, j, [&](int k, cx<T> w) { x[k] = cmul(x[k], w); });
     }
     mr_zero<T, 1, N2, !S::SPLIT>(y0);
     mr_trip<T, S::SPLIT>(
@@ -960,8 +988,7 @@ __device__ __forceinline__ void mr_spec_body(const MrArgs &a, unsigned ta, unsig
             y[k2] = cmk<T>((T)(-mu * (double)y[k2].y), (T)(mu * (double)y[k2].x));
         }
         DftMR<T, N2, MR_S2>::run(y);
-#pragma unroll
-        for (int k = 1; k < N2; ++k) y[k] = cmul(y[k], mr_ld<T>(tw, j * k * CS));
+        mr_twiddles<T, N2, sizeof(T) == 4 ? 8 : 0>(tw, j, [&](int k, cx<T> w) { y[k] = cmul(y[k], w); });
     }
     __syncthreads();  // the first exchange is read before the second overwrites it
     mr_zero<T, 1, N1, !S::SPLIT>(x0);
@@ -1019,19 +1046,22 @@ __device__ __forceinline__ void mr_x_items(F f) {
     }
 }
 
-// From the step-0 outputs x[it] of the items (c, q) to the last step's, handed to
-// put(it, c, i, v), whose outputs are the points i + J o of line c.  Every thread
-// calls this; LDS is free on entry (all reads done) and on return holds nothing of use.
-template <typename T, class P, int NT, int I0, typename PUT>
-__device__ __forceinline__ void mr_x_steps(cx<T> (&x)[I0][P::G(0)], const cx<T> *tw, PUT put) {
+// Step-0 outputs x of item (c, q) to the exchange tile.
+template <typename T, class P>
+__device__ __forceinline__ void mr_x_put(const cx<T> (&x)[P::G(0)], int c, int q) {
+    cx<T> *lds = reinterpret_cast<cx<T> *>(pf_smem);
+#pragma unroll
+    for (int o = 0; o < P::G(0); ++o) lds[(c * P::G(0) + o) * MrShape<T, P>::P2 + q] = x[o];
+}
+
+// From the exchange tile (mr_x_put of every item) to the last step's outputs, handed
+// to put(v, J): v[it] of item (c, i) holds the points i + J o of line c.  Every thread calls this.
+template <typename T, class P, int NT, typename PUT>
+__device__ __forceinline__ void mr_x_steps(const cx<T> *tw, PUT put) {
     using S = MrShape<T, P>;
-    constexpr int N = S::N, G0 = S::G0, G1 = S::G1, G2 = S::G2, J0 = N / G0, J1 = N / G1, J2 = N / G2;
+    constexpr int N = S::N, G0 = S::G0, G1 = S::G1, G2 = S::G2, J1 = N / G1, J2 = N / G2;
     constexpr int I1 = (S::XP * J1 + NT - 1) / NT, I2 = (S::XP * J2 + NT - 1) / NT;
     cx<T> *lds = reinterpret_cast<cx<T> *>(pf_smem);
-    mr_x_items<S::XP, J0, NT>([&](int it, int c, int q) {
-#pragma unroll
-        for (int o = 0; o < G0; ++o) lds[(c * G0 + o) * S::P2 + q] = x[it][o];
-    });
     __syncthreads();
     cx<T> y[I1][G1];
     mr_x_items<S::XP, J1, NT>([&](int it, int c, int i) {
@@ -1072,22 +1102,23 @@ __device__ __forceinline__ void mr_r2c_body(const MrArgs &a, unsigned tile, unsi
     const cx<T> *tw = reinterpret_cast<const cx<T> *>(a.tw);
     const T *in = reinterpret_cast<const T *>(a.in) + (size_t)g0 * N;
     cx<T> *out = reinterpret_cast<cx<T> *>(a.out) + mr_rows<T, S::XP>(a, g0, row) * C;
-    cx<T> x[(S::XP * J0 + NT - 1) / NT][G0];
-    mr_x_items<S::XP, J0, NT>([&](int it, int c, int q) {  // step 0: lanes along the points of the lines
+    mr_x_items<S::XP, J0, NT>([&](int, int c, int q) {  // step 0: lanes along the points of the lines
         const unsigned ga = g0 + 2 * c;
+        cx<T> x[G0];
 #pragma unroll
-        for (int m = 0; m < G0; ++m) x[it][m] = cmk<T>(T(0), T(0));
+        for (int m = 0; m < G0; ++m) x[m] = cmk<T>(T(0), T(0));
         if (ga < lines) {
 #pragma unroll
-            for (int m = 0; m < G0; ++m) x[it][m].x = mr_ld1<T>(in, (2 * c * N + q + J0 * m) * RS);
+            for (int m = 0; m < G0; ++m) x[m].x = mr_ld1<T>(in, (2 * c * N + q + J0 * m) * RS);
         }
         if (ga + 1 < lines) {
 #pragma unroll
-            for (int m = 0; m < G0; ++m) x[it][m].y = mr_ld1<T>(in, ((2 * c + 1) * N + q + J0 * m) * RS);
+            for (int m = 0; m < G0; ++m) x[m].y = mr_ld1<T>(in, ((2 * c + 1) * N + q + J0 * m) * RS);
         }
-        P::template step<0, true>(x[it], q, tw);
+        P::template step<0, true>(x, q, tw);
+        mr_x_put<T, P>(x, c, q);
     });
-    mr_x_steps<T, P, NT>(x, tw, [&](auto &v, auto jc) {
+    mr_x_steps<T, P, NT>(tw, [&](auto &v, auto jc) {
         constexpr int J = decltype(jc)::value;
         __syncthreads();  // the exchange tile is read before the spectra overwrite it
         mr_x_items<S::XP, J, NT>([&](int it, int c, int i) {
@@ -1183,8 +1214,9 @@ __device__ __forceinline__ void mr_c2r_body(const MrArgs &a, unsigned tile, unsi
         P::template step<0, true>(x[it], q, tw);
     });
     __syncthreads();  // the lines are read before the exchange tile overwrites them
+    mr_x_items<S::XP, J0, NT>([&](int it, int c, int q) { mr_x_put<T, P>(x[it], c, q); });
     // last step: real parts to line 2c, minus imaginary to 2c + 1
-    mr_x_steps<T, P, NT>(x, tw, [&](auto &v, auto jc) {
+    mr_x_steps<T, P, NT>(tw, [&](auto &v, auto jc) {
         constexpr int J = decltype(jc)::value;
         auto store = [&](auto nt) {
             constexpr bool NTS = decltype(nt)::value;
@@ -1235,7 +1267,7 @@ __global__ __launch_bounds__((MrShape<T, MrTwoStep<T, N1, N2>>::CTHREADS)) void 
 }
 
 template <class P, int FWD, typename T>
-__global__ __launch_bounds__((MrShape<T, P>::XTHREADS)) void k_mr_x(MrArgs m) {
+__global__ __launch_bounds__((MrShape<T, P>::XTHREADS), (MrShape<T, P>::XWAVES)) void k_mr_x(MrArgs m) {
     MrArgs a;
     const unsigned tile = mr_resolve(m, a);
     constexpr int NT = MrShape<T, P>::XTHREADS;
