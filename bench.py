@@ -172,7 +172,7 @@ def summarize_trace(trace_csv: str, command: str, steps: int, warmup: int) -> No
             "(synth.batch_sizes(4, 64), 7-smooth sizes in [48, 320]^3)", *head,
             f"modes serial, serial + hipGraph, serial on 4 streams, fused, fused + hipGraph, fused on 4 "
             f"streams, with default and tuned plans: {pairs} pairs each;",
-            "k_mr_c2c<N1, N2, T> / k_mr_x<N1, N2, FWD, T>: the compile-time mixed-radix passes (length N1 N2; "
+            "k_mr_c2c<PLAN, T> / k_mr_x<PLAN, FWD, T>: the compile-time mixed-radix passes (plan of a length; "
             "one launch per transform and pass in",
             "the serial modes; fused: k_mr_c2c_class / k_mr_x_class, one launch per pass and class of lengths); "
             "k_*_b: fused launches of the runtime-radix passes (one per pass and block size),",
