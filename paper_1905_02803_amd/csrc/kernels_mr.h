@@ -20,8 +20,8 @@
 //
 // Bound by the HBM traffic of the pass; measured against the runtime-radix
 // kernels, which staged the tile in LDS and read their twiddles per radix stage
-// (ms per R2C + C2R pair): FP64 300 x 280 x 250 0.675 -> 0.360 (Y pass 2.55 ->
-// 6.1 TB/s), FP64 600 x 400 x 450 3.95 -> 2.20, FP32 768 x 768 x 384 3.27 ->
+// (ms per R2C + C2R pair): FP64 300 x 280 x 250 0.675 -> 0.365 (Y pass 2.55 ->
+// 6.0 TB/s), FP64 600 x 400 x 450 3.95 -> 2.20, FP32 768 x 768 x 384 3.27 ->
 // 2.37, FP32 384^3 in natural order 0.897 -> 0.616, FP32 36 x 20 x 24 0.049 ->
 // 0.020 (8.2 against 2.9 us per pass on the device).
 //
@@ -360,7 +360,7 @@ constexpr MrStages mr_stages(int n) {
 // ---- global accesses -------------------------------------------------------------
 // A workgroup-uniform base pointer and a 32-bit byte offset per lane: one address
 // register per access in flight instead of two, which is what bounds how many
-// waves fit (18 x 20 in FP32: 114 registers with 64-bit addresses, 81 so).  The planner
+// waves fit (18 x 20 in FP32: 114 registers with 64-bit addresses, 84 so).  The planner
 // keeps passes whose tiles span 4 GB or more on the runtime-radix kernels.  The bases are qualified as global memory: they come from the
 // plan's arguments or a batch's table, so the compiler cannot tell that they are
 // not LDS, and would make flat accesses, which also take the LDS path and its
@@ -915,10 +915,10 @@ __device__ __forceinline__ void mr_c2c_body(const MrArgs &a, unsigned ta, unsign
 // with it are computed in FP64 for either precision and rounded once.
 // Replaces a chain of Z pass, product, Z pass (and two weight passes of the
 // adjoint), each over the whole array: the step and its adjoint at 320 x 300 x
-// 181 took 765 us in FP32 and 1804 us in FP64, now 365 and 622; 24 x 70 x 71,
-// 16 launches, 137 and 199 us, now 10 launches, 57 .. 62 us.  The FP32
-// extensions of 256 points and more stay on the power-of-two kernels: 512 x 512
-// x 257 takes 1.24 ms there (split DCT, 0.18 ms) against 1.51 here (0.33 ms).
+// 181 took 768 us in FP32 and 1800 us in FP64, now 356 .. 369 and 615 .. 626; 24 x
+// 70 x 71, 16 launches, 100 and 92 us, now 10 launches, 34 and 35 us.  The FP32
+// extensions that are powers of two from 256 on stay on the power-of-two kernels:
+// 512 x 512 x 257 takes 1.24 ms there (split DCT, 0.18 ms) against 1.51 here (0.33).
 template <typename T, int N1, int N2>
 __device__ __forceinline__ void mr_spec_body(const MrArgs &a, unsigned ta, unsigned cb) {
     using S = MrShape<T, MrTwoStep<T, N1, N2>>;
